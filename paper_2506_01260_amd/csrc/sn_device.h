@@ -35,6 +35,17 @@ template <> __device__ __forceinline__ bf16_t from_f32<bf16_t>(float v) {
   return static_cast<bf16_t>(pack_bf16x2(v, 0.0f) & 0xFFFFu);
 }
 
+// float64 -> bf16, round to nearest even, without double rounding: round to
+// float by truncation, make the float odd when that was inexact (round to
+// odd keeps the information RNE at 8 bits needs: Boldo and Melquiond,
+// "Emulation of FMA and correctly rounded sums: proved algorithms using
+// rounding to odd", IEEE Trans. Computers 57(4), 2008), then RNE to bf16.
+__device__ __forceinline__ bf16_t bf16_from_f64(double x) {
+  float f = __double2float_rz(x);
+  if (static_cast<double>(f) != x && x == x) f = __uint_as_float(__float_as_uint(f) | 1u);
+  return from_f32<bf16_t>(f);
+}
+
 // unpack the two bf16 halves of a dword to float
 __device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
@@ -61,30 +72,8 @@ struct Dot2 {
     add(p);
     c = __fadd_rn(c, e);
   }
-  __device__ __forceinline__ void merge(float os, float oc) {
-    add(os);
-    c = __fadd_rn(c, oc);
-  }
   __device__ __forceinline__ float value() const { return __fadd_rn(s, c); }
 };
-
-// Sum a Dot2 over the 64 lanes of a wave (every lane gets the result).
-__device__ __forceinline__ float wave_sum_dot2(Dot2 a) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const float os = __shfl_xor(a.s, off, 64);
-    const float oc = __shfl_xor(a.c, off, 64);
-    a.merge(os, oc);
-  }
-  return a.value();
-}
-
-// ---- wave64 reduction -----------------------------------------------------
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
 
 // ---- id handling: clamp out-of-range ids, flag them ----------------------
 // bit 0: token id outside [0, vocab); bit 1: position id outside [0, n_pos)

@@ -1,10 +1,16 @@
-// Basis packing and the generic (vector-ALU) codec kernels.
+// Basis packing and the generic codec kernels (float64 matrix cores).
 //
 // The generic kernels handle every shape, stride and dtype the ABI accepts:
-// all float32 work, and bf16 work that does not meet the MFMA kernels'
-// alignment / size conditions.  Every sum is a compensated (Dot2) float32
-// accumulation, rounded once to the output type, so float32 results stay
-// within a few units in the last place even when the sum cancels.
+// all float32 work, and bf16 work that does not meet the bf16 MFMA kernels'
+// alignment / size conditions.  Products and sums are float64 (a float32
+// product is exact there), rounded once to the output type, so float32
+// results stay within a rounding of the exact value even when the sum cancels.
+//
+// v_mfma_f64_16x16x4_f64 (wave64): lane l = 16 g + n supplies A[n][g] and
+// B[g][n] and receives D[4 i + g][n], i = 0..3.  The contraction indices may
+// be dealt to (step, g) in any order, as long as A and B agree.
+#include <type_traits>
+
 #include "sn_device.h"
 #include "sn_internal.h"
 
@@ -25,6 +31,10 @@ PackLayout pack_layout(int64_t d, int64_t k, int dt) {
   size_t off = 0;
   L.off_f32 = off;
   off = align256(off + static_cast<size_t>(d) * k * 4);
+  L.off_kfrag32 = off;
+  off = align256(off + static_cast<size_t>(ceil_div(d, 32)) * L.kt * 2048);
+  L.off_rfrag32 = off;
+  off = align256(off + static_cast<size_t>(ceil_div(d, 16)) * L.kt * 1024);
   if (L.mfma) {
     L.off_kfrag = off;
     off = align256(off + static_cast<size_t>(d / 32) * L.kt * 1024);
@@ -50,6 +60,37 @@ __global__ __launch_bounds__(256) void pack_f32_kernel(const T *__restrict__ U, 
   if (idx >= d * k) return;
   int64_t r = idx / k, j = idx - r * k;
   out[idx] = to_f32(U[r * ldu + j]);
+}
+
+// The float32 fragment sections, one thread per 16-byte slot: kfrag32 slots
+// first, then rfrag32's.
+template <typename T>
+__global__ __launch_bounds__(256) void pack_frag32_kernel(const T *__restrict__ U, int64_t d,
+                                                          int64_t k, int64_t ldu, int kt,
+                                                          f32x4 *__restrict__ kfrag,
+                                                          f32x4 *__restrict__ rfrag) {
+  int64_t slot = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  const int64_t nk = (d + 31) / 32 * kt * 128, nr = (d + 15) / 16 * kt * 64;
+  const bool second = slot >= nk;
+  if (second) slot -= nk;
+  if (second && slot >= nr) return;
+  const int lane = static_cast<int>(slot & 63), g = lane >> 4, n = lane & 15;
+  f32x4 v;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    int64_t row, col;
+    if (!second) {
+      const int64_t blk = slot >> 7;
+      row = 32 * (blk / kt) + 8 * g + 4 * ((slot >> 6) & 1) + e;
+      col = 16 * (blk % kt) + n;
+    } else {
+      const int64_t blk = slot >> 6;
+      row = 16 * (blk / kt) + 4 * (n & 3) + (n >> 2);
+      col = 16 * (blk % kt) + 4 * e + g;
+    }
+    v[e] = row < d && col < k ? to_f32(U[row * ldu + col]) : 0.0f;
+  }
+  (second ? rfrag : kfrag)[slot] = v;
 }
 
 // One thread per 8-element lane slot of a 1 KiB fragment block.
@@ -145,6 +186,18 @@ hipError_t launch_pack(const PackLayout &L, const void *U, int64_t ldu, void *pa
   else
     pack_f32_kernel<bf16_t><<<grid, 256, 0, s>>>(static_cast<const bf16_t *>(U), L.d, L.k, ldu,
                                                  reinterpret_cast<float *>(base + L.off_f32));
+  {
+    const int64_t slots = ceil_div(L.d, 32) * L.kt * 128 + ceil_div(L.d, 16) * L.kt * 64;
+    const dim3 gf(static_cast<unsigned>(ceil_div(slots, 256)));
+    f32x4 *kf = reinterpret_cast<f32x4 *>(base + L.off_kfrag32);
+    f32x4 *rf = reinterpret_cast<f32x4 *>(base + L.off_rfrag32);
+    if (L.dt == 0)
+      pack_frag32_kernel<float><<<gf, 256, 0, s>>>(static_cast<const float *>(U), L.d, L.k, ldu,
+                                                   L.kt, kf, rf);
+    else
+      pack_frag32_kernel<bf16_t><<<gf, 256, 0, s>>>(static_cast<const bf16_t *>(U), L.d, L.k, ldu,
+                                                    L.kt, kf, rf);
+  }
   if (L.mfma) {
     const bf16_t *Ub = static_cast<const bf16_t *>(U);
     int64_t slots = (L.d / 32) * L.kt * 64;
@@ -167,18 +220,82 @@ hipError_t launch_pack(const PackLayout &L, const void *U, int64_t ldu, void *pa
 }
 
 // ---------------------------------------------------------------------------
-// Token / position row resolution shared by the generic kernels
+// Helpers of the float64 matrix-core kernels
 // ---------------------------------------------------------------------------
 
-template <typename T>
-struct Rows {
-  const T *e;  // T_fixed row of the token, or nullptr
-  const T *p;  // positional row, or nullptr
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f64x4 mfma64(double a, double b, f64x4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+template <typename T> __device__ __forceinline__ T from_f64(double v);
+template <> __device__ __forceinline__ float from_f64<float>(double v) {
+  return static_cast<float>(v);
+}
+template <> __device__ __forceinline__ bf16_t from_f64<bf16_t>(double v) {
+  return bf16_from_f64(v);
+}
+
+// 8 consecutive elements of a row as two vectors; rows need only be aligned
+// to their element size (the memory pipeline takes unaligned vector loads).
+template <typename T> struct Row8;
+template <> struct Row8<float> {
+  typedef float v4 __attribute__((ext_vector_type(4), aligned(4)));
+  v4 a, b;
+  __device__ __forceinline__ void load(const float *p) {
+    a = *reinterpret_cast<const v4 *>(p);
+    b = *reinterpret_cast<const v4 *>(p + 4);
+  }
+  __device__ __forceinline__ double at(int i) const { return i < 4 ? a[i & 3] : b[i & 3]; }
+};
+template <> struct Row8<bf16_t> {
+  typedef uint32_t v4 __attribute__((ext_vector_type(4), aligned(2)));
+  v4 a;
+  __device__ __forceinline__ void load(const bf16_t *p) { a = *reinterpret_cast<const v4 *>(p); }
+  __device__ __forceinline__ double at(int i) const {
+    const uint32_t w = a[i >> 1];
+    return (i & 1) ? bf_hi(w) : bf_lo(w);
+  }
 };
 
+// 4 consecutive elements, element-aligned
+template <typename T> struct Row4;
+template <> struct Row4<float> {
+  typedef float v4 __attribute__((ext_vector_type(4), aligned(4)));
+  v4 a;
+  __device__ __forceinline__ void load(const float *p) { a = *reinterpret_cast<const v4 *>(p); }
+  __device__ __forceinline__ double at(int i) const { return a[i]; }
+  static __device__ __forceinline__ void store(float *p, f64x4 v) {
+    *reinterpret_cast<v4 *>(p) = v4{static_cast<float>(v.x), static_cast<float>(v.y),
+                                    static_cast<float>(v.z), static_cast<float>(v.w)};
+  }
+};
+template <> struct Row4<bf16_t> {
+  typedef uint32_t v2 __attribute__((ext_vector_type(2), aligned(2)));
+  v2 a;
+  __device__ __forceinline__ void load(const bf16_t *p) { a = *reinterpret_cast<const v2 *>(p); }
+  __device__ __forceinline__ double at(int i) const {
+    const uint32_t w = a[i >> 1];
+    return (i & 1) ? bf_hi(w) : bf_lo(w);
+  }
+  static __device__ __forceinline__ void store(bf16_t *p, f64x4 v) {
+    uint32_t h[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) h[i] = bf16_from_f64(v[i]);
+    *reinterpret_cast<v2 *>(p) = v2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
+  }
+};
+
+// Token and positional rows of token i; a missing table gives the row `none`
+// (any readable row of d elements, whose values are not used).
 template <typename T>
-__device__ __forceinline__ Rows<T> resolve_rows(int64_t i, const IdArgs &a) {
-  Rows<T> r{nullptr, nullptr};
+struct Rows {
+  const T *e, *p;
+};
+template <typename T>
+__device__ __forceinline__ Rows<T> resolve_rows(int64_t i, const IdArgs &a, const T *none) {
+  Rows<T> r{none, none};
   if (a.E) {
     int64_t t = clamp_id(a.tok[i], a.vocab, a.err_flag, 1);
     r.e = static_cast<const T *>(a.E) + t * a.lde;
@@ -192,66 +309,235 @@ __device__ __forceinline__ Rows<T> resolve_rows(int64_t i, const IdArgs &a) {
 }
 
 // ---------------------------------------------------------------------------
-// Compress: one wave per token.  Each lane strides over d, accumulates up to
-// 8 columns of C at a time, and the wave reduces with cross-lane shuffles.
+// Compress: (X - P - E) U for 16 tokens per workgroup, the NW waves taking
+// every NW-th unit of 32 columns of d and adding their sums through LDS in
+// wave order.  X - P - E is formed in float64 (no rounding that float32 could
+// see), one f64 MFMA per 4 columns and 16 columns of U.
+//
+// Bound by the f64 matrix rate (75 TFLOP/s measured in a loop of MFMAs) from
+// k ~ 16 up, below that by HBM.  16-token tiles alone leave the chip idle
+// below ~16000 tokens, hence the split of d over the waves; a unit's loads (16
+// rows x 128 contiguous bytes) keep whole cache lines, and a wave's rows of
+// the next unit are loaded while it multiplies.  8192 tokens, d = 2048,
+// k = 20, float32: 355 us (one wave per token on the vector ALU, compensated
+// sums) -> 21 us, MFMAs alone 14.
 // ---------------------------------------------------------------------------
 
-template <typename T>
-__global__ __launch_bounds__(256) void compress_generic_kernel(const float *__restrict__ Uf,
-                                                               int64_t d, int64_t k,
-                                                               const T *__restrict__ X,
-                                                               int64_t N, int64_t ldx, IdArgs ids,
-                                                               T *__restrict__ C, int64_t ldc) {
+// What becomes of the sums: the output type (after subtracting projected rows
+// if there are any), fp32 rows of a projected table (ldc = its padded width,
+// zero past k), or float64 rows.
+enum GenOut { kGenT = 0, kGenTable = 1, kGenF64 = 2 };
+
+template <typename T, int KT, int NW, bool TAB>
+__global__ __launch_bounds__(64 * NW) void compress_f64_kernel(
+    const f32x4 *__restrict__ kfrag, int kt, int64_t d, int64_t k, const T *__restrict__ X,
+    int64_t N, int64_t ldx, IdArgs ids, ProjArgs pa, int mode, void *__restrict__ out,
+    int64_t ldc) {
+  constexpr int TC = 16 / NW < KT ? 16 / NW : KT;  // column tiles reduced at a time (32 KiB)
+  __shared__ double red[NW][TC][64][4];
   const int lane = threadIdx.x & 63;
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-  if (i >= N) return;
-  const Rows<T> rw = resolve_rows<T>(i, ids);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 4, n = lane & 15;
+  const int64_t i0 = 16 * static_cast<int64_t>(blockIdx.x);
+  const int64_t i = i0 + n < N ? i0 + n : N - 1;  // rows past N repeat the last, not stored
+  const int t0 = static_cast<int>(blockIdx.y) * KT;  // first column tile
   const T *xr = X + i * ldx;
-  // (X - P - E) U is summed as X U - P U - E U: no rounding of X - P - E.
-  for (int64_t j0 = 0; j0 < k; j0 += 8) {
-    Dot2 acc[8];
-    const int jn = static_cast<int>(k - j0 < 8 ? k - j0 : 8);
-    for (int64_t r = lane; r < d; r += 64) {
-      const float x = to_f32(xr[r]);
-      const float p = rw.p ? -to_f32(rw.p[r]) : 0.0f;
-      const float e = rw.e ? -to_f32(rw.e[r]) : 0.0f;
-      const float *ur = Uf + r * k + j0;
+  Rows<T> rw{};
+  if constexpr (TAB) rw = resolve_rows<T>(i, ids, xr);
+  const bool he = TAB && ids.E, hp = TAB && ids.P;
+
+  f64x4 acc[KT];
 #pragma unroll
-      for (int jj = 0; jj < 8; ++jj) {
-        if (jj < jn) {
-          acc[jj].add_prod(x, ur[jj]);
-          if (rw.p) acc[jj].add_prod(p, ur[jj]);
-          if (rw.e) acc[jj].add_prod(e, ur[jj]);
-        }
+  for (int t = 0; t < KT; ++t) acc[t] = f64x4{0., 0., 0., 0.};
+
+  auto frag = [&](int u, int t, int h) {
+    const int tt = t0 + t < kt ? t0 + t : kt - 1;  // tiles past the last are not stored
+    return kfrag[((static_cast<int64_t>(u) * kt + tt) * 2 + h) * 64 + lane];
+  };
+  // a lane's 8 columns 32 u + 8 g .. + 7 of its rows and, while they are few,
+  // the unit's U fragments
+  constexpr bool kPre = KT <= 2;
+  struct Unit {
+    Row8<T> x, e, p;
+    f32x4 a[kPre ? KT : 1][2];
+  };
+  auto load = [&](Unit &v, int u) {
+    const int64_t c = 32 * static_cast<int64_t>(u) + 8 * g;
+    v.x.load(xr + c);
+    if constexpr (TAB) {
+      v.e.load(rw.e + c);
+      v.p.load(rw.p + c);
+    }
+    if constexpr (kPre) {
+#pragma unroll
+      for (int t = 0; t < KT; ++t)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) v.a[t][h] = frag(u, t, h);
+    }
+  };
+  auto value = [&](const Unit &v, int j) {
+    double x = v.x.at(j);
+    if constexpr (TAB) {
+      const double p = v.p.at(j), e = v.e.at(j);
+      x -= hp ? p : 0.0;
+      x -= he ? e : 0.0;
+    }
+    return x;
+  };
+  auto step = [&](const Unit &v, int u) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      f32x4 a[KT];
+#pragma unroll
+      for (int t = 0; t < KT; ++t) {
+        if constexpr (kPre)
+          a[t] = v.a[t][h];
+        else
+          a[t] = frag(u, t, h);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const double b = value(v, 4 * h + e);
+#pragma unroll
+        for (int t = 0; t < KT; ++t) acc[t] = mfma64(static_cast<double>(a[t][e]), b, acc[t]);
       }
     }
-#pragma unroll
-    for (int jj = 0; jj < 8; ++jj) {
-      const float v = wave_sum_dot2(acc[jj]);
-      if (lane == 0 && jj < jn) C[i * ldc + j0 + jj] = from_f32<T>(v);
+  };
+
+  const int nfull = static_cast<int>(d / 32);
+  if (wave < nfull) {
+    Unit cur, nxt;
+    load(cur, wave);
+    for (int u = wave; u < nfull; u += NW) {
+      load(nxt, u + NW < nfull ? u + NW : u);  // past the end the unit repeats, unused
+      step(cur, u);
+      cur = nxt;
     }
   }
+  if (d % 32 != 0 && wave == nfull % NW) {  // the last, partial unit: zero past column d
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int64_t c = 32 * static_cast<int64_t>(nfull) + 8 * g + j;
+      double x = 0.0;
+      if (c < d) {
+        x = to_f32(xr[c]);
+        if (hp) x -= static_cast<double>(to_f32(rw.p[c]));
+        if (he) x -= static_cast<double>(to_f32(rw.e[c]));
+      }
+#pragma unroll
+      for (int t = 0; t < KT; ++t)
+        acc[t] = mfma64(static_cast<double>(frag(nfull, t, j >> 2)[j & 3]), x, acc[t]);
+    }
+  }
+
+  // lane (g, n) holds columns 16 t + 4 i + g of token n
+#pragma unroll
+  for (int tc = 0; tc < KT; tc += TC) {
+    if (tc > 0) __syncthreads();
+#pragma unroll
+    for (int t = 0; t < TC; ++t)
+      if (tc + t < KT) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) red[wave][t][lane][q] = acc[tc + t < KT ? tc + t : 0][q];
+      }
+    __syncthreads();
+    for (int idx = threadIdx.x; idx < TC * 256; idx += 64 * NW) {
+      const int nn = idx / (16 * TC), jl = idx % (16 * TC);
+      const int t = jl >> 4, q = (jl & 15) >> 2, gg = jl & 3;
+      const int64_t j = 16 * static_cast<int64_t>(t0 + tc) + jl;
+      const int64_t tok = i0 + nn;
+      if (tc + t >= KT || tok >= N || j >= (mode == kGenTable ? ldc : k)) continue;
+      double v = red[0][t][16 * gg + nn][q];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) v += red[w][t][16 * gg + nn][q];
+      if (mode == kGenTable) {
+        static_cast<float *>(out)[tok * ldc + j] = static_cast<float>(v);
+      } else if (mode == kGenF64) {
+        static_cast<double *>(out)[tok * ldc + j] = v;
+      } else {
+        if (pa.pu) {
+          int64_t p = pa.pos ? static_cast<int64_t>(pa.pos[tok]) : tok % pa.seq_len;
+          v -= static_cast<double>(pa.pu[clamp_id(p, pa.n_pos, pa.err_flag, 2) * pa.kp + j]);
+        }
+        if (pa.eu)
+          v -= static_cast<double>(
+              pa.eu[clamp_id(pa.tok[tok], pa.vocab, pa.err_flag, 1) * pa.kp + j]);
+        static_cast<T *>(out)[tok * ldc + j] = from_f64<T>(v);
+      }
+    }
+  }
+}
+
+// Workgroups take KT column tiles of U each: as many as still leave a
+// workgroup for every CU (a launch of few tokens splits the columns, and with
+// them the MFMAs, and re-reads its rows from the caches).  Waves per
+// workgroup: so many that a CU has about 16, which hide each other's loads
+// behind the 64-cycle MFMAs (16 only while 128 registers hold the
+// accumulators, KT <= 4).  500 tokens, d = 8192, k = 82: 109 us with all
+// column tiles in one workgroup, 21.5 split; 8192 tokens: 21.3 us with 16
+// waves, 21.7 with 8, 24.2 with 4.
+template <typename T, int KT, bool TAB>
+void launch_compress_f64(const PackLayout &L, const void *packed, const void *X, int64_t N,
+                         int64_t ldx, const IdArgs &ids, const ProjArgs &pa, int mode, void *out,
+                         int64_t ldc, hipStream_t s) {
+  const f32x4 *kf =
+      reinterpret_cast<const f32x4 *>(static_cast<const char *>(packed) + L.off_kfrag32);
+  const dim3 grid(static_cast<unsigned>(ceil_div(N, 16)),
+                  static_cast<unsigned>(ceil_div(L.kt, KT)));
+  const T *x = static_cast<const T *>(X);
+  auto go = [&](auto nw) {
+    constexpr int NW = decltype(nw)::value;
+    compress_f64_kernel<T, KT, NW, TAB>
+        <<<grid, 64 * NW, 0, s>>>(kf, L.kt, L.d, L.k, x, N, ldx, ids, pa, mode, out, ldc);
+  };
+  const int64_t groups = static_cast<int64_t>(grid.x) * grid.y;
+  if (KT <= 4 && groups <= 512)
+    go(std::integral_constant<int, KT <= 4 ? 16 : 8>{});
+  else if (groups <= 1024)
+    go(std::integral_constant<int, 8>{});
+  else
+    go(std::integral_constant<int, 4>{});
+}
+
+template <typename T, bool TAB>
+hipError_t compress_f64_kt(const PackLayout &L, const void *packed, const void *X, int64_t N,
+                           int64_t ldx, const IdArgs &ids, const ProjArgs &pa, int mode, void *out,
+                           int64_t ldc, hipStream_t s) {
+  auto go = [&](auto kt) {
+    launch_compress_f64<T, decltype(kt)::value, TAB>(L, packed, X, N, ldx, ids, pa, mode, out,
+                                                     ldc, s);
+    return hipGetLastError();
+  };
+  const int64_t tiles = ceil_div(N, 16);
+  auto fits = [&](int kt) { return L.kt >= kt && tiles * ceil_div(L.kt, kt) >= 256; };
+  if (fits(7)) return go(std::integral_constant<int, 8>{});
+  if (fits(5)) return go(std::integral_constant<int, 6>{});
+  if (fits(4)) return go(std::integral_constant<int, 4>{});
+  if (fits(3)) return go(std::integral_constant<int, 3>{});
+  if (fits(2)) return go(std::integral_constant<int, 2>{});
+  return go(std::integral_constant<int, 1>{});
+}
+
+template <bool TAB>
+hipError_t compress_f64(const PackLayout &L, const void *packed, const void *X, int64_t N,
+                        int64_t ldx, const IdArgs &ids, const ProjArgs &pa, int mode, void *out,
+                        int64_t ldc, hipStream_t s) {
+  return L.dt == 0
+             ? compress_f64_kt<float, TAB>(L, packed, X, N, ldx, ids, pa, mode, out, ldc, s)
+             : compress_f64_kt<bf16_t, TAB>(L, packed, X, N, ldx, ids, pa, mode, out, ldc, s);
 }
 
 hipError_t launch_compress_generic(const PackLayout &L, const void *packed, const void *X,
                                    int64_t N, int64_t ldx, const IdArgs &ids, void *C,
                                    int64_t ldc, hipStream_t s) {
-  const float *Uf = reinterpret_cast<const float *>(static_cast<const char *>(packed) + L.off_f32);
-  dim3 grid(static_cast<unsigned>(ceil_div(N, 4)));
-  if (L.dt == 0)
-    compress_generic_kernel<float><<<grid, 256, 0, s>>>(
-        Uf, L.d, L.k, static_cast<const float *>(X), N, ldx, ids, static_cast<float *>(C), ldc);
-  else
-    compress_generic_kernel<bf16_t><<<grid, 256, 0, s>>>(
-        Uf, L.d, L.k, static_cast<const bf16_t *>(X), N, ldx, ids, static_cast<bf16_t *>(C), ldc);
-  return hipGetLastError();
+  const ProjArgs none{};
+  if (ids.E || ids.P) return compress_f64<true>(L, packed, X, N, ldx, ids, none, kGenT, C, ldc, s);
+  return compress_f64<false>(L, packed, X, N, ldx, ids, none, kGenT, C, ldc, s);
 }
 
 // ---------------------------------------------------------------------------
-// Projected tables and compress against them (one wave per row, as above).
-// TABLE: out[r, j] = (T U)[r, j] as fp32 for j < k, 0 for k <= j < kp.
-// Otherwise: C[i, j] = (X U)[i, j] - (P U)[pos_i, j] - (T_fixed U)[tok_i, j],
-// each subtraction rounded to fp32, then one rounding to the output type.
+// Projected tables and compress against them: the same kernel with other
+// ends.
 // ---------------------------------------------------------------------------
 
 ProjLayout proj_layout(int64_t k, int64_t vocab, int64_t n_pos) {
@@ -263,117 +549,190 @@ ProjLayout proj_layout(int64_t k, int64_t vocab, int64_t n_pos) {
   return P;
 }
 
-template <typename T, bool TABLE>
-__global__ __launch_bounds__(256) void project_rows_generic_kernel(
-    const float *__restrict__ Uf, int64_t d, int64_t k, const T *__restrict__ X, int64_t N,
-    int64_t ldx, ProjArgs pa, void *__restrict__ out, int64_t ldo) {
-  const int lane = threadIdx.x & 63;
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-  if (i >= N) return;
-  const T *xr = X + i * ldx;
-  const float *pr = nullptr, *er = nullptr;
-  if (!TABLE) {
-    if (pa.pu) {
-      int64_t p = pa.pos ? static_cast<int64_t>(pa.pos[i]) : i % pa.seq_len;
-      pr = pa.pu + clamp_id(p, pa.n_pos, pa.err_flag, 2) * pa.kp;
-    }
-    if (pa.eu) er = pa.eu + clamp_id(pa.tok[i], pa.vocab, pa.err_flag, 1) * pa.kp;
-  }
-  const int64_t ncols = TABLE ? ldo : k;  // a table row is written out to its padded width
-  for (int64_t j0 = 0; j0 < ncols; j0 += 8) {
-    Dot2 acc[8];
-    const int jn = static_cast<int>(k - j0 < 8 ? (k - j0 > 0 ? k - j0 : 0) : 8);
-    for (int64_t r = lane; r < d && jn > 0; r += 64) {
-      const float x = to_f32(xr[r]);
-      const float *ur = Uf + r * k + j0;
-#pragma unroll
-      for (int jj = 0; jj < 8; ++jj)
-        if (jj < jn) acc[jj].add_prod(x, ur[jj]);
-    }
-#pragma unroll
-    for (int jj = 0; jj < 8; ++jj) {
-      float v = wave_sum_dot2(acc[jj]);
-      const int64_t j = j0 + jj;
-      if (lane != 0) continue;
-      if (TABLE) {
-        if (j < ncols) static_cast<float *>(out)[i * ldo + j] = jj < jn ? v : 0.0f;
-      } else if (jj < jn) {
-        if (pr) v = __fsub_rn(v, pr[j]);
-        if (er) v = __fsub_rn(v, er[j]);
-        static_cast<T *>(out)[i * ldo + j] = from_f32<T>(v);
-      }
-    }
-  }
-}
-
 hipError_t launch_table_project_generic(const PackLayout &L, const void *packed, const void *T,
                                         int64_t rows, int64_t ldt, float *out, int64_t kp,
                                         hipStream_t s) {
-  const float *Uf = reinterpret_cast<const float *>(static_cast<const char *>(packed) + L.off_f32);
-  dim3 grid(static_cast<unsigned>(ceil_div(rows, 4)));
-  ProjArgs none{};
-  if (L.dt == 0)
-    project_rows_generic_kernel<float, true><<<grid, 256, 0, s>>>(
-        Uf, L.d, L.k, static_cast<const float *>(T), rows, ldt, none, out, kp);
-  else
-    project_rows_generic_kernel<bf16_t, true><<<grid, 256, 0, s>>>(
-        Uf, L.d, L.k, static_cast<const bf16_t *>(T), rows, ldt, none, out, kp);
-  return hipGetLastError();
+  return compress_f64<false>(L, packed, T, rows, ldt, IdArgs{}, ProjArgs{}, kGenTable, out, kp, s);
 }
 
 hipError_t launch_compress_projected_generic(const PackLayout &L, const void *packed,
                                              const void *X, int64_t N, int64_t ldx,
                                              const ProjArgs &pa, void *C, int64_t ldc,
                                              hipStream_t s) {
-  const float *Uf = reinterpret_cast<const float *>(static_cast<const char *>(packed) + L.off_f32);
-  dim3 grid(static_cast<unsigned>(ceil_div(N, 4)));
-  if (L.dt == 0)
-    project_rows_generic_kernel<float, false><<<grid, 256, 0, s>>>(
-        Uf, L.d, L.k, static_cast<const float *>(X), N, ldx, pa, C, ldc);
-  else
-    project_rows_generic_kernel<bf16_t, false><<<grid, 256, 0, s>>>(
-        Uf, L.d, L.k, static_cast<const bf16_t *>(X), N, ldx, pa, C, ldc);
-  return hipGetLastError();
+  return compress_f64<false>(L, packed, X, N, ldx, IdArgs{}, pa, kGenT, C, ldc, s);
 }
 
 // ---------------------------------------------------------------------------
-// Decompress: one thread per output element; blockIdx.x = token,
-// blockIdx.y = 256-wide slice of d.
+// Decompress: a workgroup owns 64 tokens (a tile of 16 per wave, whose
+// coefficients the wave holds in float64) and a range of column pairs (32
+// columns of d), whose U fragments it copies into LDS once.  P + E is the
+// MFMA chain's start, so the sum is rounded once; the tables' values of the
+// next pair are loaded while this one is multiplied.  A pair keeps whole
+// 128-byte lines of float32 rows together and two MFMA chains in flight.
+// Bound by the stores (3.2 TB/s at k = 4) up to k ~ 30, above by the f64
+// matrix rate.  8192 tokens, d = 2048, k = 20, float32: 305 us (a thread per
+// element) -> 21 us; neighbouring workgroups hold neighbouring columns of the
+// same rows, not other rows (32768 tokens, d = 4096, k = 40: 308 -> 218 us).
+// Fragments kept in LDS as float64 (no conversion per MFMA, twice the LDS
+// reads) took 274 us there.
 // ---------------------------------------------------------------------------
 
-template <typename T>
-__global__ __launch_bounds__(256) void decompress_generic_kernel(const float *__restrict__ Uf,
-                                                                 int64_t d, int64_t k,
-                                                                 const T *__restrict__ C,
-                                                                 int64_t ldc, IdArgs ids,
-                                                                 T *__restrict__ X, int64_t ldx) {
-  const int64_t i = blockIdx.x;
-  const int64_t r = static_cast<int64_t>(blockIdx.y) * 256 + threadIdx.x;
-  if (r >= d) return;
-  const Rows<T> rw = resolve_rows<T>(i, ids);
-  const T *cr = C + i * ldc;
-  const float *ur = Uf + r * k;
-  Dot2 acc;
-  for (int64_t j = 0; j < k; ++j) acc.add_prod(to_f32(cr[j]), ur[j]);
-  if (rw.p) acc.add(to_f32(rw.p[r]));
-  if (rw.e) acc.add(to_f32(rw.e[r]));
-  X[i * ldx + r] = from_f32<T>(acc.value());
+constexpr int kDecLds = 32 * 1024;  // U fragments per workgroup (at least one pair's)
+
+template <typename T, int KG, bool TAB>
+__global__ __launch_bounds__(256) void decompress_f64_kernel(
+    const f32x4 *__restrict__ rfrag, int kt, int64_t d, int64_t k, const T *__restrict__ C,
+    int64_t N, int64_t ldc, IdArgs ids, T *__restrict__ X, int64_t ldx, int pairs_per_wg) {
+  extern __shared__ f32x4 us[];  // [tile of the range][kt][lane]
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 4, n = lane & 15;
+  const int ntile = static_cast<int>((d + 15) / 16);
+  const int r0 = 2 * static_cast<int>(blockIdx.x) * pairs_per_wg;
+  const int r1 = r0 + 2 * pairs_per_wg < ntile ? r0 + 2 * pairs_per_wg : ntile;
+  const int64_t tg = static_cast<int64_t>(blockIdx.z) * gridDim.y + blockIdx.y;
+  if (64 * tg >= N) return;
+  {
+    const f32x4 *src = rfrag + static_cast<int64_t>(r0) * kt * 64;
+    const int units = (r1 - r0) * kt * 64;
+    for (int e = threadIdx.x; e < units; e += 256) us[e] = src[e];
+  }
+  const int64_t i = 16 * (tg * 4 + wave) + n;
+  const bool live = i < N;
+  const int64_t ic = live ? i : N - 1;
+  const int nsteps = static_cast<int>((k + 3) / 4);
+  double cb[4 * KG];  // C[token n, 4 s + g] of step s
+#pragma unroll
+  for (int st = 0; st < 4 * KG; ++st) {
+    const int64_t j = 4 * st + g;
+    cb[st] = j < k ? static_cast<double>(to_f32(C[ic * ldc + j])) : 0.0;
+  }
+  T *xr = X + ic * ldx;
+  Rows<T> rw{};
+  if constexpr (TAB) rw = resolve_rows<T>(ic, ids, static_cast<const T *>(nullptr));
+
+  // P + E of columns 16 r + 4 g .. + 3 of the token
+  struct Tab {
+    Row4<T> p, e;
+  };
+  const bool hp = TAB && ids.P, he = TAB && ids.E;
+  auto whole = [&](int r) { return 16 * static_cast<int64_t>(r) + 4 * g + 4 <= d; };
+  auto load_tab = [&](Tab &t, int r) {
+    const int64_t c = 16 * static_cast<int64_t>(r) + 4 * g;
+    if (whole(r)) {
+      if (hp) t.p.load(rw.p + c);
+      if (he) t.e.load(rw.e + c);
+    }
+  };
+  auto start = [&](const Tab &t, int r) {
+    f64x4 v = {0., 0., 0., 0.};
+    if constexpr (TAB) {
+      const int64_t c = 16 * static_cast<int64_t>(r) + 4 * g;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (whole(r)) {
+          if (hp) v[q] += t.p.at(q);
+          if (he) v[q] += t.e.at(q);
+        } else if (c + q < d) {
+          if (hp) v[q] += static_cast<double>(to_f32(rw.p[c + q]));
+          if (he) v[q] += static_cast<double>(to_f32(rw.e[c + q]));
+        }
+      }
+    }
+    return v;
+  };
+  // lane (g, n): columns 16 r + 4 g .. + 3 of token n
+  auto store = [&](int r, const f64x4 &v) {
+    const int64_t c = 16 * static_cast<int64_t>(r) + 4 * g;
+    if (whole(r)) {
+      Row4<T>::store(xr + c, v);
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (c + q < d) xr[c + q] = from_f64<T>(v[q]);
+    }
+  };
+
+  Tab cur[2], nxt[2];
+  if constexpr (TAB) {
+    load_tab(cur[0], r0);
+    load_tab(cur[1], r0 + 1);
+  }
+  __syncthreads();
+  for (int r = r0; r < r1; r += 2) {
+    if constexpr (TAB) {  // past the range the last pair's again, unused
+      const int rn = r + 2 < r1 ? r + 2 : r;
+      load_tab(nxt[0], rn);
+      load_tab(nxt[1], rn + 1);
+    }
+    f64x4 a0 = start(cur[0], r), a1 = start(cur[1], r + 1);
+    const f32x4 *f0 = us + (r - r0) * kt * 64 + lane;
+    const f32x4 *f1 = r + 1 < r1 ? f0 + kt * 64 : f0;  // an odd last tile has no partner
+#pragma unroll
+    for (int q = 0; q < KG; ++q) {
+      const int qq = q < kt ? q : kt - 1;  // groups past the last take no step below
+      const f32x4 u0 = f0[qq * 64], u1 = f1[qq * 64];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (4 * q + e < nsteps) {
+          a0 = mfma64(static_cast<double>(u0[e]), cb[4 * q + e], a0);
+          a1 = mfma64(static_cast<double>(u1[e]), cb[4 * q + e], a1);
+        }
+    }
+    if (live) {
+      store(r, a0);
+      if (r + 1 < r1) store(r + 1, a1);
+    }
+    if constexpr (TAB) {
+      cur[0] = nxt[0];
+      cur[1] = nxt[1];
+    }
+  }
+}
+
+template <typename T, bool TAB>
+hipError_t decompress_f64(const PackLayout &L, const void *packed, const void *C, int64_t N,
+                          int64_t ldc, const IdArgs &ids, void *X, int64_t ldx, hipStream_t s) {
+  const f32x4 *rf =
+      reinterpret_cast<const f32x4 *>(static_cast<const char *>(packed) + L.off_rfrag32);
+  // column ranges: about 4 workgroups (16 waves) a CU, and as many pairs as
+  // the LDS allotment holds
+  const int64_t tgroups = ceil_div(N, 64), pairs = ceil_div(L.d, 32);
+  int64_t per = ceil_div(pairs, ceil_div(1024, tgroups));
+  const int64_t most = kDecLds / (2048 * L.kt) > 0 ? kDecLds / (2048 * L.kt) : 1;
+  per = per < most ? per : most;
+  const int64_t gy = tgroups < 32768 ? tgroups : 32768;
+  const dim3 grid(static_cast<unsigned>(ceil_div(pairs, per)), static_cast<unsigned>(gy),
+                  static_cast<unsigned>(ceil_div(tgroups, gy)));
+  const T *c = static_cast<const T *>(C);
+  T *x = static_cast<T *>(X);
+  auto go = [&](auto kg) {
+    decompress_f64_kernel<T, decltype(kg)::value, TAB>
+        <<<grid, 256, static_cast<size_t>(per) * 2048 * L.kt, s>>>(
+            rf, L.kt, L.d, L.k, c, N, ldc, ids, x, ldx, static_cast<int>(per));
+    return hipGetLastError();
+  };
+  switch (L.kt) {
+    case 1: return go(std::integral_constant<int, 1>{});
+    case 2: return go(std::integral_constant<int, 2>{});
+    case 3: return go(std::integral_constant<int, 3>{});
+    case 4: return go(std::integral_constant<int, 4>{});
+    case 5:
+    case 6: return go(std::integral_constant<int, 6>{});
+    case 7:
+    case 8: return go(std::integral_constant<int, 8>{});
+    default: return go(std::integral_constant<int, 16>{});
+  }
 }
 
 hipError_t launch_decompress_generic(const PackLayout &L, const void *packed, const void *C,
                                      int64_t N, int64_t ldc, const IdArgs &ids, void *X,
                                      int64_t ldx, hipStream_t s) {
-  const float *Uf = reinterpret_cast<const float *>(static_cast<const char *>(packed) + L.off_f32);
-  const int64_t ychunks = ceil_div(L.d, 256);
-  // gridDim.x holds the tokens (up to 2^31-1), gridDim.y the d slices.
-  dim3 grid(static_cast<unsigned>(N), static_cast<unsigned>(ychunks));
-  if (L.dt == 0)
-    decompress_generic_kernel<float><<<grid, 256, 0, s>>>(
-        Uf, L.d, L.k, static_cast<const float *>(C), ldc, ids, static_cast<float *>(X), ldx);
-  else
-    decompress_generic_kernel<bf16_t><<<grid, 256, 0, s>>>(
-        Uf, L.d, L.k, static_cast<const bf16_t *>(C), ldc, ids, static_cast<bf16_t *>(X), ldx);
-  return hipGetLastError();
+  if (ids.E || ids.P)
+    return L.dt == 0 ? decompress_f64<float, true>(L, packed, C, N, ldc, ids, X, ldx, s)
+                     : decompress_f64<bf16_t, true>(L, packed, C, N, ldc, ids, X, ldx, s);
+  return L.dt == 0 ? decompress_f64<float, false>(L, packed, C, N, ldc, ids, X, ldx, s)
+                   : decompress_f64<bf16_t, false>(L, packed, C, N, ldc, ids, X, ldx, s);
 }
 
 // ---------------------------------------------------------------------------

@@ -140,17 +140,6 @@ __device__ __forceinline__ double block_sum256(double v, double *red) {
   return red[0];
 }
 
-// float64 -> bf16, round to nearest even, without double rounding: round to
-// float by truncation, make the float odd when that was inexact (round to
-// odd keeps the information RNE at 8 bits needs: Boldo and Melquiond,
-// "Emulation of FMA and correctly rounded sums: proved algorithms using
-// rounding to odd", IEEE Trans. Computers 57(4), 2008), then RNE to bf16.
-__device__ __forceinline__ bf16_t bf16_from_f64(double x) {
-  float f = __double2float_rz(x);
-  if (static_cast<double>(f) != x && x == x) f = __uint_as_float(__float_as_uint(f) | 1u);
-  return from_f32<bf16_t>(f);
-}
-
 // ---------------------------------------------------------------------------
 // state
 // ---------------------------------------------------------------------------

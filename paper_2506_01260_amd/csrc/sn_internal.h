@@ -16,7 +16,15 @@ inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 // Packed basis (one device buffer, sections 256-byte aligned):
 //
-//  f32   U as float32, d x k, row stride k.  Read by the generic kernels.
+//  f32   U as float32, d x k, row stride k.
+//  kfrag32, rfrag32  U as float32 in the operand layouts of the generic
+//        kernels' float64 MFMAs (zero past row d and column k).  kfrag32
+//        (contraction over d): 2 KiB blocks [ceil(d/32)][ceil(k/16)]; lane
+//        l = 16 g + n of half h holds U[32 s + 8 g + 4 h + e, 16 t + n],
+//        e = 0..3.  rfrag32 (contraction over k): 1 KiB blocks
+//        [ceil(d/16)][ceil(k/16)]; lane l = 16 g + m holds
+//        U[16 r + 4 (m%4) + m/4, 16 q + 4 e + g], e = 0..3: the row order puts
+//        4 consecutive d-rows of one token in one lane of the result.
 //  kfrag (bf16 and d % 32 == 0 and k <= 128 only) U in the MFMA operand layout
 //        of a contraction over d (compress, projection pass 1): 1 KiB blocks
 //        indexed [s][t], s = d/32 row steps, t = ceil(k/16) column tiles;
@@ -41,7 +49,7 @@ struct PackLayout {
   int kt = 0;   // ceil(k/16)
   int ks = 0;   // ceil(k/32)
   int ks2 = 0;  // ceil(2k/32) when the uu section exists, else 0
-  size_t off_f32 = 0, off_kfrag = 0, off_rfrag = 0, off_uu = 0, off_gram = 0, total = 0;
+  size_t off_f32 = 0, off_kfrag32 = 0, off_rfrag32 = 0, off_kfrag = 0, off_rfrag = 0, off_uu = 0, off_gram = 0, total = 0;
 };
 
 PackLayout pack_layout(int64_t d, int64_t k, int dt);

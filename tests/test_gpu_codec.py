@@ -355,6 +355,46 @@ def test_shapes(dtype, d, k, n):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("tables", ["EP", "E", "P", ""])
+@pytest.mark.parametrize("d,k,n,pad", [(7, 3, 5, 0), (31, 4, 16, 1), (33, 15, 65, 3), (49, 17, 63, 0),
+                                       (95, 49, 64, 5), (161, 33, 4200, 0), (100, 97, 17, 1),
+                                       (300, 129, 130, 2), (257, 256, 33, 0)])
+def test_generic_kernel_edges(dtype, d, k, n, pad, tables):
+    """The float64 matrix-core kernels at the edges of their tiles: widths
+    around 16 and 32 columns (and below one unit), column tiles of U that are
+    part-filled or split over workgroups, token tiles of every occupancy, few
+    and many workgroups, odd row strides.  float32 results are one rounding
+    (2^-24 of the value) off the exact sum, up to the sum's own cancellation:
+    2^-22 of max(|value|, row rms)."""
+    log(f"[generic] {dtype} d={d} k={k} n={n} pad={pad} tables={tables!r}")
+    st, o, tok, pos = _small(d, k, n, dtype=dtype, seed=d + k + n)
+    basis = sn.sn_basis_pack(dev(st["U"], dtype))
+
+    def padded(a):  # the same values at a row stride of cols + pad
+        t = dev(a, dtype)
+        buf = torch.full((t.shape[0], t.shape[1] + pad), float("nan"), dtype=t.dtype, device="cuda")
+        buf[:, :t.shape[1]] = t
+        return buf[:, :t.shape[1]]
+
+    E, P = (padded(st[x]) if x in tables else None for x in "EP")
+    oE, oP = (o[x] if x in tables else None for x in "EP")
+    where = dict(tok=ids(tok), seq_len=9)
+    X, C = padded(st["X"]), padded(st["C"])
+    got_c = sn.sn_compress(basis, X, E=E, P=P, **where)
+    got_x = sn.sn_decompress(basis, C, E=E, P=P, **where)
+    proj = sn.sn_embed_project(basis, E=E, P=P)
+    got_p = sn.sn_compress_projected(basis, X, proj, **where)
+    ref_c = oracle.compress(o["X"], o["U"], tok, oE, oP, seq_len=9)
+    ref_x = oracle.decompress(o["C"], o["U"], tok, oE, oP, seq_len=9)
+    for got, ref, what in ((got_c, ref_c, "compress"), (got_p, ref_c, "projected"),
+                           (got_x, ref_x, "decompress")):
+        assert_parity(host(got), oracle.round_to(ref, dtype), dtype, what)
+        if dtype == "f32" and what != "projected":
+            tol = 2.0 ** -22 * np.maximum(np.abs(ref), np.sqrt(np.mean(ref * ref, -1, keepdims=True)))
+            assert np.all(np.abs(host(got) - ref) <= tol), what
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_tables_optional_and_explicit_positions(dtype):
     d, k, n = 256, 24, 70
     st, o, tok, _ = _small(d, k, n, dtype=dtype, seed=5)
