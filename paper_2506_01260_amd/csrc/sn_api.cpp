@@ -246,10 +246,7 @@ int32_t sn_compress(const void *basis, int64_t d, int64_t k, int32_t dt, const v
     return st;
   const sn::IdArgs ids = make_ids(tok, E, vocab, lde, pos, P, n_pos, ldp, seq_len, err_flag);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (sn::compress_mfma_ok(L, X, ldx, ids))
-    return hip_status(sn::launch_compress_mfma(L, basis, X, N, ldx, ids, C, ldc, s),
-                      "sn_compress launch");
-  return hip_status(sn::launch_compress_generic(L, basis, X, N, ldx, ids, C, ldc, s),
+  return hip_status(sn::launch_compress(L, basis, X, N, ldx, ids, C, ldc, s),
                     "sn_compress launch");
 }
 
@@ -335,10 +332,8 @@ int32_t sn_embed_project(const void *basis, int64_t d, int64_t k, int32_t dt, co
   for (const auto &pt : parts) {
     if (pt.rows == 0) continue;
     float *o = reinterpret_cast<float *>(base + pt.off);
-    hipError_t e = sn::stream_mfma_ok(L, pt.t, pt.ld)
-                       ? sn::launch_table_project_mfma(L, basis, pt.t, pt.rows, pt.ld, o, PL.kp, s)
-                       : sn::launch_table_project_generic(L, basis, pt.t, pt.rows, pt.ld, o,
-                                                          PL.kp, s);
+    const hipError_t e =
+        sn::launch_table_project(L, basis, pt.t, pt.rows, pt.ld, o, PL.kp, s);
     if (e != hipSuccess) return hip_status(e, "sn_embed_project launch");
   }
   return ok();
@@ -397,10 +392,7 @@ int32_t sn_compress_projected(const void *basis, int64_t d, int64_t k, int32_t d
   pa.kp = PL.kp;
   pa.err_flag = err_flag;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (sn::stream_mfma_ok(L, X, ldx))
-    return hip_status(sn::launch_compress_projected_mfma(L, basis, X, N, ldx, pa, C, ldc, s),
-                      "sn_compress_projected launch");
-  return hip_status(sn::launch_compress_projected_generic(L, basis, X, N, ldx, pa, C, ldc, s),
+  return hip_status(sn::launch_compress_projected(L, basis, X, N, ldx, pa, C, ldc, s),
                     "sn_compress_projected launch");
 }
 

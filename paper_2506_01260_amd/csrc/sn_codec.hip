@@ -963,11 +963,6 @@ void launch_c_kt(const bf16_t *kf, const PackLayout &L, const void *X, int64_t l
 
 }  // namespace
 
-bool compress_mfma_ok(const PackLayout &L, const void *X, int64_t ldx, const IdArgs &ids) {
-  if (!ids.E && !ids.P) return stream_mfma_ok(L, X, ldx);
-  return L.mfma && L.d % kStageCols == 0 && aligned16(X) && ldx % 8 == 0 && tables_ok(ids);
-}
-
 hipError_t launch_compress_mfma(const PackLayout &L, const void *packed, const void *X,
                                 int64_t N, int64_t ldx, const IdArgs &ids, void *C, int64_t ldc,
                                 hipStream_t s) {
@@ -1006,7 +1001,60 @@ hipError_t launch_compress_projected_mfma(const PackLayout &L, const void *packe
   return launch_plain<kEpiProjected>(L, packed, X, N, ldx, pa, C, ldc, s);
 }
 
+// Whether the few-token kernel (one workgroup per 16 tokens) takes a compress
+// of N tokens: while its workgroups fit one round on the CUs, two rounds while
+// U is narrow (its re-reads grow with k).  d = 4096, k = 40, both tables: 4096
+// tokens 15 us against 37 in compress_kernel, 8192 tokens 33 / 37; d = 8192,
+// k = 82: 43 / 76 and 84 / 77; d = 4096, k = 40, no tables, 8192 tokens
+// 16 / 20; d = 2048, k = 20, 16384 tokens 17.6 / 14.4.
+bool split_preferred(const PackLayout &L, int64_t N) {
+  return ceil_div(N, 16) <= static_cast<int64_t>(device_cus()) * (L.kt <= 4 ? 2 : 1);
+}
+
+// The subspace update's compress has no register-ring form, so where d is no
+// multiple of 64 the few-token kernel takes it at every N.
+bool grass_split(const PackLayout &L, int64_t N) {
+  return split_preferred(L, N) || L.d % kStageCols != 0;
+}
+
+bool grass_writes_wire(const PackLayout &L, int64_t N) {
+  return grass_split(L, N) == split_preferred(L, N);
+}
+
+hipError_t launch_compress(const PackLayout &L, const void *packed, const void *X, int64_t N,
+                           int64_t ldx, const IdArgs &ids, void *C, int64_t ldc, hipStream_t s) {
+  if (!stream_mfma_ok(L, X, ldx) || !tables_ok(ids))
+    return launch_compress_generic(L, packed, X, N, ldx, ids, C, ldc, s);
+  // with tables compress_kernel takes whole stages of 64 columns only
+  if (split_preferred(L, N) || ((ids.E || ids.P) && L.d % kStageCols != 0))
+    return launch_compress_split(L, packed, X, N, ldx, ids, C, ldc, s);
+  return launch_compress_mfma(L, packed, X, N, ldx, ids, C, ldc, s);
+}
+
+hipError_t launch_table_project(const PackLayout &L, const void *packed, const void *T,
+                                int64_t rows, int64_t ldt, float *out, int64_t kp, hipStream_t s) {
+  if (!stream_mfma_ok(L, T, ldt))
+    return launch_table_project_generic(L, packed, T, rows, ldt, out, kp, s);
+  if (split_preferred(L, rows))
+    return launch_table_project_split(L, packed, T, rows, ldt, out, kp, s);
+  return launch_table_project_mfma(L, packed, T, rows, ldt, out, kp, s);
+}
+
+hipError_t launch_compress_projected(const PackLayout &L, const void *packed, const void *X,
+                                     int64_t N, int64_t ldx, const ProjArgs &pa, void *C,
+                                     int64_t ldc, hipStream_t s) {
+  if (!stream_mfma_ok(L, X, ldx))
+    return launch_compress_projected_generic(L, packed, X, N, ldx, pa, C, ldc, s);
+  if (split_preferred(L, N))
+    return launch_compress_projected_split(L, packed, X, N, ldx, pa, C, ldc, s);
+  return launch_compress_projected_mfma(L, packed, X, N, ldx, pa, C, ldc, s);
+}
+
 int64_t grass_compress_groups(const PackLayout &L, int64_t N, int64_t *steps) {
+  if (grass_split(L, N)) {  // two workgroups of 16 tokens per step
+    if (steps) *steps = ceil_div(N, 32);
+    return 2 * ceil_div(N, 32);
+  }
   int nw = 4;
   switch (L.kt) {
     case 1: nw = pick_nw<1, false, false, 1>(N); break;
@@ -1027,7 +1075,9 @@ int64_t grass_compress_groups(const PackLayout &L, int64_t N, int64_t *steps) {
 hipError_t launch_grass_compress_mfma(const PackLayout &L, const void *packed, const void *G,
                                       int64_t N, int64_t ldg, const GrassOut &go, void *Cwire,
                                       int64_t ldc, hipStream_t s) {
-  if (!L.mfma || L.d % kStageCols != 0) return hipErrorNotSupported;
+  if (!L.mfma) return hipErrorNotSupported;
+  if (grass_split(L, N))
+    return launch_grass_compress_split(L, packed, G, N, ldg, go, Cwire, ldc, s);
   const bf16_t *kf =
       reinterpret_cast<const bf16_t *>(static_cast<const char *>(packed) + L.off_kfrag);
   const int cvec = Cwire && ((reinterpret_cast<uintptr_t>(Cwire) & 7) == 0) && (ldc % 4 == 0);

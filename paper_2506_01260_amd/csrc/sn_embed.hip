@@ -348,9 +348,7 @@ hipError_t launch_embed_backward(const PackLayout &L, const void *packed, const 
   const EmbedPlan P = embed_plan(L.k, L.dt, N, vocab, true);
   char *w = static_cast<char *>(ws);
   float *c32 = reinterpret_cast<float *>(w + P.off_c);
-  hipError_t e = stream_mfma_ok(L, dX0, ldg)
-                     ? launch_table_project_mfma(L, packed, dX0, N, ldg, c32, P.kp, s)
-                     : launch_table_project_generic(L, packed, dX0, N, ldg, c32, P.kp, s);
+  hipError_t e = launch_table_project(L, packed, dX0, N, ldg, c32, P.kp, s);
   if (e != hipSuccess) return e;
   auto I = [&](size_t off) { return reinterpret_cast<int32_t *>(w + off); };
   double *part = reinterpret_cast<double *>(w + P.off_part);

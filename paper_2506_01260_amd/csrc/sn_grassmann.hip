@@ -14,8 +14,8 @@
 // which is exact for any stored U; with D = U^T U - I (a section of the
 // packed basis) the row term is |g|^2 - |c|^2 + c D c^T.
 //
-// MFMA path (bf16, d a multiple of 64, k <= 128), per accumulate:
-//   1. the staged compress kernel with the subspace-update epilogue: per row
+// MFMA path (bf16, d a multiple of 32, k <= 128), per accumulate:
+//   1. the gradient compress's kernel with the subspace-update epilogue: per row
 //      |g|^2 (summed with the stages), c = g U, and the loss term (c D c^T
 //      on the matrix cores), summed per workgroup; C split into bf16 hi + lo
 //      in the MFMA operand layout of a contraction over tokens (through
@@ -48,14 +48,14 @@ struct AccPlan {
   int64_t rows = 0;    // tokens per split, a multiple of 128
   int64_t npad = 0;    // ds * rows >= N
   int64_t m_pad = 0;   // d rounded up to 128
-  int64_t nlblk = 0;   // loss partials (at most one per 64 rows on the MFMA path, 256 on the generic)
+  int64_t nlblk = 0;   // loss partials (at most one per 16 rows on the MFMA path, 256 on the generic)
   size_t off_c = 0, off_frag = 0, off_part = 0, off_tp = 0, total = 0;
 };
 
 AccPlan acc_plan(const PackLayout &L, int64_t N, bool mfma) {
   AccPlan P;
   P.mfma = mfma;
-  P.nlblk = mfma ? ceil_div(N, 64) : ceil_div(N, 256);
+  P.nlblk = mfma ? 2 * ceil_div(N, 32) : ceil_div(N, 256);
   size_t off = 0;
   if (mfma) {
     P.kt = L.kt;
@@ -417,12 +417,12 @@ size_t grass_state_bytes(int64_t d, int64_t k) {
 }
 
 bool grass_mfma_ok(const PackLayout &L, const void *G, int64_t ldg) {
-  return L.mfma && L.d % 64 == 0 && aligned16(G) && ldg % 8 == 0;
+  return L.mfma && aligned16(G) && ldg % 8 == 0;
 }
 
 size_t grass_workspace_bytes(const PackLayout &L, int64_t N) {
   size_t w = acc_plan(L, N, false).total;
-  if (L.mfma && L.d % 64 == 0) {
+  if (L.mfma) {
     const size_t m = acc_plan(L, N, true).total;
     w = m > w ? m : w;
   }
@@ -461,8 +461,14 @@ hipError_t launch_grass_accumulate(const PackLayout &L, const void *packed, cons
     go.npad = P.npad;
     int64_t steps = 0;
     const int64_t nlblk = grass_compress_groups(L, N, &steps);
-    hipError_t e = launch_grass_compress_mfma(L, packed, G, N, ldg, go, Cwire, ldc, s);
+    const bool wire = grass_writes_wire(L, N);
+    hipError_t e =
+        launch_grass_compress_mfma(L, packed, G, N, ldg, go, wire ? Cwire : nullptr, ldc, s);
     if (e != hipSuccess) return e;
+    if (Cwire && !wire) {
+      e = launch_compress(L, packed, G, N, ldg, IdArgs{}, Cwire, ldc, s);
+      if (e != hipSuccess) return e;
+    }
     if (with_su && steps < P.npad / 32) {
       const int64_t per_part = (P.npad / 32) * P.ktb * 512;  // bf16 per operand
       const int64_t tail = (P.npad / 32 - steps) * P.ktb * 512 / 4;  // as doubles
@@ -508,10 +514,7 @@ hipError_t launch_grass_accumulate(const PackLayout &L, const void *packed, cons
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   if (Cwire) {
     // the coefficients for the wire, by the kernel the gradient compress uses
-    const IdArgs none{};
-    if (compress_mfma_ok(L, G, ldg, none))
-      return launch_compress_mfma(L, packed, G, N, ldg, none, Cwire, ldc, s);
-    return launch_compress_generic(L, packed, G, N, ldg, none, Cwire, ldc, s);
+    return launch_compress(L, packed, G, N, ldg, IdArgs{}, Cwire, ldc, s);
   }
   return hipSuccess;
 }

@@ -89,9 +89,16 @@ struct IdArgs {
 hipError_t launch_pack(const PackLayout &L, const void *U, int64_t ldu, void *packed,
                        hipStream_t s);
 
+// The compress of any shape: picks among the kernels below.
+hipError_t launch_compress(const PackLayout &L, const void *packed, const void *X, int64_t N,
+                           int64_t ldx, const IdArgs &ids, void *C, int64_t ldc, hipStream_t s);
 hipError_t launch_compress_generic(const PackLayout &L, const void *packed, const void *X,
                                    int64_t N, int64_t ldx, const IdArgs &ids, void *C,
                                    int64_t ldc, hipStream_t s);
+// bf16 (L.mfma) of few tokens
+hipError_t launch_compress_split(const PackLayout &L, const void *packed, const void *X, int64_t N,
+                                 int64_t ldx, const IdArgs &ids, void *C, int64_t ldc,
+                                 hipStream_t s);
 hipError_t launch_decompress_generic(const PackLayout &L, const void *packed, const void *C,
                                      int64_t N, int64_t ldc, const IdArgs &ids, void *X,
                                      int64_t ldx, hipStream_t s);
@@ -102,7 +109,6 @@ hipError_t launch_project_generic(const PackLayout &L, const void *packed, void 
 
 // MFMA paths (bf16, L.mfma).  Return hipErrorNotSupported if the arguments do
 // not fit the fast path; the caller then uses the generic kernels.
-bool compress_mfma_ok(const PackLayout &L, const void *X, int64_t ldx, const IdArgs &ids);
 hipError_t launch_compress_mfma(const PackLayout &L, const void *packed, const void *X,
                                 int64_t N, int64_t ldx, const IdArgs &ids, void *C, int64_t ldc,
                                 hipStream_t s);
@@ -137,6 +143,19 @@ struct ProjArgs {
   int32_t *err_flag;
 };
 
+// rows x d table -> rows x kp fp32 (T U), and the compress against such
+// tables, of any shape
+hipError_t launch_table_project(const PackLayout &L, const void *packed, const void *T,
+                                int64_t rows, int64_t ldt, float *out, int64_t kp, hipStream_t s);
+hipError_t launch_compress_projected(const PackLayout &L, const void *packed, const void *X,
+                                     int64_t N, int64_t ldx, const ProjArgs &pa, void *C,
+                                     int64_t ldc, hipStream_t s);
+hipError_t launch_table_project_split(const PackLayout &L, const void *packed, const void *T,
+                                      int64_t rows, int64_t ldt, float *out, int64_t kp,
+                                      hipStream_t s);
+hipError_t launch_compress_projected_split(const PackLayout &L, const void *packed, const void *X,
+                                           int64_t N, int64_t ldx, const ProjArgs &pa, void *C,
+                                           int64_t ldc, hipStream_t s);
 bool stream_mfma_ok(const PackLayout &L, const void *X, int64_t ldx);
 // rows x d table -> rows x kp fp32 (T U), MFMA path
 hipError_t launch_table_project_mfma(const PackLayout &L, const void *packed, const void *T,
@@ -171,6 +190,12 @@ struct GrassOut {
 hipError_t launch_grass_compress_mfma(const PackLayout &L, const void *packed, const void *G,
                                       int64_t N, int64_t ldg, const GrassOut &go, void *Cwire,
                                       int64_t ldc, hipStream_t s);
+hipError_t launch_grass_compress_split(const PackLayout &L, const void *packed, const void *G,
+                                       int64_t N, int64_t ldg, const GrassOut &go, void *Cwire,
+                                       int64_t ldc, hipStream_t s);
+// Whether launch_grass_compress_mfma's wire coefficients are the gradient
+// compress's bit for bit (the same kernel's sums).
+bool grass_writes_wire(const PackLayout &L, int64_t N);
 // Workgroups (loss partials) of that compress for N rows, and 32-row steps
 // of the operand it writes.
 int64_t grass_compress_groups(const PackLayout &L, int64_t N, int64_t *steps);

@@ -394,6 +394,49 @@ def test_generic_kernel_edges(dtype, d, k, n, pad, tables):
             assert np.all(np.abs(host(got) - ref) <= tol), what
 
 
+@pytest.mark.parametrize("tables", ["EP", "E", "P", ""])
+@pytest.mark.parametrize("d,k,n", [(32, 7, 5), (64, 16, 33), (96, 33, 1), (480, 40, 17), (544, 128, 100),
+                                   (1056, 100, 31), (288, 20, 8200), (256, 65, 4096),
+                                   (320, 65, 4097), (256, 40, 8192), (256, 40, 8193)])
+def test_few_token_compress_and_narrow_blocks(d, k, n, tables):
+    """The few-token compress: fewer units of 64 columns than waves, an odd last
+    step of 32, part-filled token tiles, every column-tile count class, and the
+    token counts on both sides of its dispatch (one and two rounds of
+    workgroups); the decompress of widths that are no multiple of 256 (the
+    last column block overlaps its neighbour).  The wire coefficients of the
+    subspace update stay those of the gradient compress."""
+    log(f"[few tokens] d={d} k={k} n={n} tables={tables!r}")
+    st, o, tok, pos = _small(d, min(k, d), n, dtype="bf16", seed=d + k + n)
+    k = min(k, d)
+    basis = sn.sn_basis_pack(dev(st["U"], "bf16"))
+    E, P = (dev(st[x], "bf16") if x in tables else None for x in "EP")
+    oE, oP = (o[x] if x in tables else None for x in "EP")
+    where = dict(tok=ids(tok), pos=ids(pos))
+    C = sn.sn_compress(basis, dev(st["X"], "bf16"), E=E, P=P, **where)
+    ref_c = oracle.compress(o["X"], o["U"], tok, oE, oP, pos=pos)
+    assert_parity(host(C), oracle.round_to(ref_c, "bf16"), "bf16", "compress")
+    Xr = sn.sn_decompress(basis, dev(st["C"], "bf16"), E=E, P=P, **where)
+    ref_x = oracle.decompress(o["C"], o["U"], tok, oE, oP, pos=pos)
+    assert_parity(host(Xr), oracle.round_to(ref_x, "bf16"), "bf16", "decompress")
+    if tables == "":
+        G = dev(st["G"], "bf16")
+        state = sn.sn_grassmann_state(basis)
+        cg = sn.sn_grassmann_accumulate(basis, G, state, want_cg=True)
+        assert torch.equal(cg.view(torch.int16), sn.sn_grad_compress(basis, G).view(torch.int16))
+        c64 = o["G"] @ o["U"]
+        loss = float(np.sum((o["G"] - c64 @ o["U"].T) ** 2))
+        assert abs(float(state.scalars()[0]) - loss) <= 1e-5 * float(np.sum(o["G"] ** 2))
+        # C enters the token contraction as bf16 hi + lo (2^-18 of each value),
+        # summed in fp32 in chains of at most 32 steps of 32 tokens (2^-19 of
+        # the terms) before float64 takes over
+        err = np.abs(state.Y().cpu().numpy() - o["G"].T @ c64)
+        assert np.all(err <= 2.0 ** -17 * (np.abs(o["G"]).T @ np.abs(c64)))
+    else:
+        proj = sn.sn_embed_project(basis, E=E, P=P)
+        got = sn.sn_compress_projected(basis, dev(st["X"], "bf16"), proj, **where)
+        assert_parity(host(got), oracle.round_to(ref_c, "bf16"), "bf16", "projected")
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_tables_optional_and_explicit_positions(dtype):
     d, k, n = 256, 24, 70
