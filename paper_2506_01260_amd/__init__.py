@@ -2,7 +2,10 @@
 
 Argument marshalling only: each function turns torch tensors into the plain
 pointers, sizes and strides of the C ABI in ``include/sn.h`` (same names) and
-launches on the current torch stream.  Every step of the codec runs in the
+launches on the current torch stream.  The functions of the training loop hand
+an ordinary call to native code first (``_calls``, which does the same checks
+and steps aside, before any launch, for whatever it does not take); the Python
+form below it makes every other call and raises every error.  Every step of the codec runs in the
 library's HIP kernels; there is no fallback.  If the library has not been
 built the first call raises ``RuntimeError``.
 
@@ -41,6 +44,7 @@ STATUS = {0: "SN_OK", 1: "SN_ERR_NULL", 2: "SN_ERR_SHAPE", 3: "SN_ERR_DTYPE", 4:
           9: "SN_ERR_WORKSPACE"}
 
 _lib = None
+_bound = None  # the native calls, once the library is loaded
 
 _P = ctypes.c_void_p
 _I64 = ctypes.c_int64
@@ -114,7 +118,7 @@ class SnError(RuntimeError):
 
 def lib():
     """The loaded libsn.so (built by paper_2506_01260_amd.build)."""
-    global _lib
+    global _lib, _bound
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(f"{LIB_PATH} is not built; run paper_2506_01260_amd.build.build()")
@@ -123,8 +127,24 @@ def lib():
             fn = getattr(L, name)
             fn.restype = res
             fn.argtypes = args
-        _lib = L
+        try:
+            from . import _calls as native
+        except ImportError as e:
+            raise RuntimeError("the native calls are not built; run "
+                               "paper_2506_01260_amd.build.build()") from e
+        native.bind({name: ctypes.cast(getattr(L, name), _P).value for name in _SIGNATURES}, _check)
+        _lib, _bound = L, native
     return _lib
+
+
+def _native():
+    """The native calls, or None while ids are checked (every call then waits
+    for its flag)."""
+    if _CHECK_IDS:
+        return None
+    if _bound is None:
+        lib()
+    return _bound
 
 
 def _check(status: int):
@@ -255,6 +275,11 @@ def _out_shape(out, shape, name):
 def sn_compress(basis: Basis, X: torch.Tensor, tok=None, E=None, P=None, pos=None,
                 seq_len=None, out=None, err_flag=None, stream=None) -> torch.Tensor:
     """C = (X - P[pos] - E[tok]) U."""
+    native = _native()
+    if native is not None:
+        C = native.compress(basis, X, tok, E, P, pos, seq_len, out, err_flag, stream)
+        if C is not None:
+            return C
     xp, N, d, ldx = _mat(X, "X")
     _same_d(basis, d, ("E", E), ("P", P))
     if out is None:
@@ -273,6 +298,11 @@ def sn_compress(basis: Basis, X: torch.Tensor, tok=None, E=None, P=None, pos=Non
 def sn_decompress(basis: Basis, C: torch.Tensor, tok=None, E=None, P=None, pos=None,
                   seq_len=None, out=None, err_flag=None, stream=None) -> torch.Tensor:
     """X = C U^T + P[pos] + E[tok]; with no tables, the gradient recovery C U^T."""
+    native = _native()
+    if native is not None:
+        X = native.decompress(basis, C, tok, E, P, pos, seq_len, out, err_flag, stream)
+        if X is not None:
+            return X
     cp, N, k, ldc = _mat(C, "C")
     if k != basis.k:
         raise SnError(2, f"C has {k} columns, basis has k = {basis.k}")
@@ -293,6 +323,11 @@ def sn_decompress(basis: Basis, C: torch.Tensor, tok=None, E=None, P=None, pos=N
 
 def sn_grad_compress(basis: Basis, G: torch.Tensor, out=None, stream=None) -> torch.Tensor:
     """Cg = G U."""
+    native = _native()
+    if native is not None:
+        Cg = native.grad_compress(basis, G, out, stream)
+        if Cg is not None:
+            return Cg
     gp, N, d, ldg = _mat(G, "G")
     _same_d(basis, d)
     if out is None:
@@ -352,6 +387,11 @@ def sn_embed_project(basis: Basis, E=None, P=None, stream=None) -> Projected:
 def sn_compress_projected(basis: Basis, X: torch.Tensor, proj: Projected, tok=None, pos=None,
                           seq_len=None, out=None, err_flag=None, stream=None) -> torch.Tensor:
     """C = X U - (P U)[pos] - (T_fixed U)[tok] against tables from sn_embed_project."""
+    native = _native()
+    if native is not None:
+        C = native.compress_projected(basis, X, proj, tok, pos, seq_len, out, err_flag, stream)
+        if C is not None:
+            return C
     xp, N, d, ldx = _mat(X, "X")
     _same_d(basis, d)
     if proj.basis is not basis:
@@ -379,6 +419,9 @@ def sn_project_weights_workspace_bytes(d: int, k: int, dt: int, m: int) -> int:
 
 def sn_project_weights(basis: Basis, W: torch.Tensor, workspace=None, stream=None) -> torch.Tensor:
     """W <- U (U^T W) in place; returns W."""
+    native = _native()
+    if native is not None and native.project_weights(basis, W, workspace, stream) is not None:
+        return W
     wp, d, m, ldw = _mat(W, "W")
     if d != basis.d:
         raise SnError(2, f"W has {d} rows, basis has d = {basis.d}")
@@ -418,6 +461,9 @@ def sn_project_weights_multi_workspace_bytes(d: int, k: int, dt: int, widths) ->
 def sn_project_weights_multi(basis: Basis, Ws, workspace=None, stream=None):
     """W <- U (U^T W) in place for every matrix of the list Ws (each d x m_i),
     in one set of launches when the widths allow; returns Ws."""
+    native = _native()
+    if native is not None and native.project_weights_multi(basis, Ws, workspace, stream) is not None:
+        return Ws
     ptrs, widths, lds = [], [], []
     for i, W in enumerate(Ws):
         wp, d, m, ldw = _mat(W, f"W[{i}]")
@@ -499,6 +545,11 @@ def sn_grassmann_accumulate(basis: Basis, G: torch.Tensor, state: GrassmannState
     """Add one iteration's gradient G (N x d) to the state: the off-subspace
     loss always, Y += G^T (G U) when with_su.  With want_cg (or out given)
     also returns the gradient coefficients G U as sn_grad_compress writes them."""
+    native = _native()
+    if native is not None and (want_cg or out is not None):
+        Cg = native.grassmann_accumulate(basis, G, state, with_su, want_cg, out, workspace, stream)
+        if Cg is not None:
+            return Cg
     gp, N, d, ldg = _mat(G, "G")
     _same_d(basis, d)
     if (state.d, state.k) != (basis.d, basis.k):
@@ -545,6 +596,12 @@ def sn_embed_lowrank_forward(basis: Basis, CS: torch.Tensor, tok: torch.Tensor, 
                              pos=None, seq_len=None, out=None, err_flag=None, workspace=None,
                              stream=None) -> torch.Tensor:
     """X0 = P[pos] + E[tok] + CS[tok] U^T (the low-rank token table T_S = CS U^T)."""
+    native = _native()
+    if native is not None:
+        X0 = native.embed_lowrank_forward(basis, CS, tok, E, P, pos, seq_len, out, err_flag,
+                                          workspace, stream)
+        if X0 is not None:
+            return X0
     cp, vocab, k, ldcs = _mat(CS, "CS")
     if k != basis.k:
         raise SnError(2, f"CS has {k} columns, basis has k = {basis.k}")
@@ -576,6 +633,10 @@ def sn_embed_lowrank_forward(basis: Basis, CS: torch.Tensor, tok: torch.Tensor, 
 def sn_embed_lowrank_backward(basis: Basis, dX0: torch.Tensor, tok: torch.Tensor, gCS: torch.Tensor,
                               err_flag=None, workspace=None, stream=None) -> torch.Tensor:
     """gCS += scatter over tok of dX0 U (float32 gCS, vocab x k); returns gCS."""
+    native = _native()
+    if native is not None and native.embed_lowrank_backward(basis, dX0, tok, gCS, err_flag,
+                                                            workspace, stream) is not None:
+        return gCS
     gp, N, d, ldg = _mat(dX0, "dX0")
     _same_d(basis, d)
     _same_dtype(basis, ("dX0", dX0))
@@ -606,6 +667,10 @@ def sn_adamw_step(W: torch.Tensor, G: torch.Tensor, M: torch.Tensor, V: torch.Te
                   stream=None) -> torch.Tensor:
     """One AdamW step in place on W (rows x cols, stored [out, in]) with fp32
     moments M, V; subspace=True uses the column-constant rate of Sec. 5."""
+    native = _native()
+    if native is not None and native.adamw_step(W, G, M, V, t, lr, beta1, beta2, eps, weight_decay,
+                                                subspace, workspace, stream) is not None:
+        return W
     wp, rows, cols, ldw = _mat(W, "W")
     gp, gr, gc, ldg = _mat(G, "G")
     mp, mr, mc, ldm = _mat(M, "M")

@@ -1,4 +1,5 @@
-"""Builds libsn.so (the codec's C-ABI library) for gfx950 with hipcc.
+"""Builds libsn.so (the codec's C-ABI library) for gfx950 with hipcc, and the
+binding's native calls with g++.
 
     python -m paper_2506_01260_amd.build        # or: from ... import build; build.build()
 
@@ -63,7 +64,35 @@ def build(jobs: int = 8) -> str:
     if r.returncode != 0:
         raise RuntimeError(f"link failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
     os.replace(tmp, LIB)
+    build_calls()
     return LIB
+
+
+# The binding's native calls (csrc/binding/py_calls.cpp): host code against the
+# installed torch's headers, imported by the package as _calls.
+CALLS = os.path.join(PKG, "_calls.so")
+
+
+def build_calls() -> str:
+    import sysconfig
+
+    import torch
+    gxx = shutil.which("g++")
+    if not gxx:
+        raise RuntimeError("g++ not found")
+    tdir = os.path.dirname(torch.__file__)
+    tmp = CALLS + ".tmp"
+    cmd = [gxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+           "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f"-I{tdir}/include", "-I/opt/rocm/include", f"-I{sysconfig.get_path('include')}",
+           f"-I{INCLUDE}", os.path.join(CSRC, "binding", "py_calls.cpp"), "-o", tmp,
+           f"-L{tdir}/lib", "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{r.stderr}")
+    os.replace(tmp, CALLS)
+    return CALLS
 
 
 # ---------------------------------------------------------------------------

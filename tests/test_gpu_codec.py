@@ -831,3 +831,62 @@ def test_id_check_mode_raises_index_error():
     sn.sn_compress(basis, X, tok=ids(bad_tok), E=E, P=P, seq_len=9, err_flag=flag)
     torch.cuda.synchronize()
     assert int(flag.item()) == 1
+
+
+def test_native_calls_and_python_form_agree(monkeypatch):
+    """Each call through the native marshalling and through the Python form of
+    the same function: bit-equal results, and what the native form leaves to
+    Python (a wrong dtype, shape, stride, an odd object) raises there."""
+    d, k, n = 256, 24, 70
+    st, o, tok, pos = _small(d, k, n, dtype="bf16", seed=3)
+    basis = sn.sn_basis_pack(dev(st["U"], "bf16"))
+    X, C, E, P, G = (dev(st[x], "bf16") for x in ("X", "C", "E", "P", "G"))
+    t, p = ids(tok), ids(pos)
+    proj = sn.sn_embed_project(basis, E=E, P=P)
+    CS = dev(synth.store(o["E"] @ o["U"], "bf16"), "bf16")
+    side = torch.cuda.Stream()
+    W0 = torch.randn(d, 264, device="cuda").bfloat16()
+    M0, V0 = torch.rand(d, 264, device="cuda"), torch.rand(d, 264, device="cuda")
+
+    def every():
+        W, W1, W2 = W0.clone(), W0.clone(), W0[:, :256].clone()
+        M, V, A = M0.clone(), V0.clone(), W0.clone()
+        state = sn.sn_grassmann_state(basis)
+        gcs = torch.zeros(E.shape[0], k, device="cuda")
+        pad = torch.zeros(n, k + 3, device="cuda", dtype=torch.bfloat16)
+        side.wait_stream(torch.cuda.current_stream())
+        got = [sn.sn_compress(basis, X, tok=t, E=E, P=P, seq_len=9),
+               sn.sn_compress(basis, X, tok=t, E=E, P=P, pos=p, out=pad[:, :k]), pad,
+               sn.sn_compress(basis, X, P=P, pos=p), sn.sn_decompress(basis, C, tok=t, E=E),
+               sn.sn_decompress(basis, C, tok=t, E=E, P=P, seq_len=9, stream=side),
+               sn.sn_decompress(basis, C), sn.sn_grad_compress(basis, G),
+               sn.sn_compress_projected(basis, X, proj, tok=t, seq_len=9),
+               sn.sn_project_weights(basis, W), *sn.sn_project_weights_multi(basis, [W1, W2]),
+               sn.sn_grassmann_accumulate(basis, G, state, want_cg=True), state.buf.clone(),
+               sn.sn_embed_lowrank_forward(basis, CS, t, E=E, P=P, pos=p),
+               sn.sn_embed_lowrank_backward(basis, G, t, gcs),
+               sn.sn_adamw_step(A, W0, M, V, 3, 1e-3, weight_decay=0.1), M, V]
+        torch.cuda.synchronize()
+        return [g.clone() for g in got]
+
+    native = every()
+    monkeypatch.setattr(sn, "_native", lambda: None)
+    python = every()
+    for i, (a, b) in enumerate(zip(native, python)):
+        assert a.dtype == b.dtype and a.shape == b.shape
+        assert torch.equal(a.contiguous().view(torch.uint8), b.contiguous().view(torch.uint8)), i
+    monkeypatch.undo()
+
+    calls = sn._native()
+    assert calls.grad_compress(basis, G.float(), None, None) is None
+    assert calls.grad_compress(basis, G.t(), None, None) is None
+    assert calls.grad_compress(basis, [1], None, None) is None
+    assert calls.grad_compress(object(), G, None, None) is None
+    for bad, status in ((lambda: sn.sn_grad_compress(basis, G.float()), 3),
+                        (lambda: sn.sn_grad_compress(basis, G[:, :-1]), 2),
+                        (lambda: sn.sn_compress(basis, X, tok=t[:-1], E=E), 2),
+                        (lambda: sn.sn_compress(basis, X, P=P, seq_len=0), 2),
+                        (lambda: sn.sn_grad_compress(basis, G, out=G[:, :k]), 5)):
+        with pytest.raises(sn.SnError) as e:
+            bad()
+        assert e.value.status == status
