@@ -68,7 +68,7 @@ def build(jobs: int = 8) -> str:
     return LIB
 
 
-# The binding's native calls (csrc/binding/py_calls.cpp): host code against the
+# The binding's native calls (native/py_calls.cpp): host code against the
 # installed torch's headers, imported by the package as _calls.
 CALLS = os.path.join(PKG, "_calls.so")
 
@@ -86,7 +86,7 @@ def build_calls() -> str:
            "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            f"-I{tdir}/include", "-I/opt/rocm/include", f"-I{sysconfig.get_path('include')}",
-           f"-I{INCLUDE}", os.path.join(CSRC, "binding", "py_calls.cpp"), "-o", tmp,
+           f"-I{INCLUDE}", os.path.join(PKG, "native", "py_calls.cpp"), "-o", tmp,
            f"-L{tdir}/lib", "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
