@@ -736,103 +736,418 @@ hipError_t launch_decompress_generic(const PackLayout &L, const void *packed, co
 }
 
 // ---------------------------------------------------------------------------
-// Weight projection W <- U (U^T W), generic path, three passes:
-//   1. partial T_s = U[rows of split s]^T W[rows of split s]   (fp32, per split)
-//   2. T = sum_s T_s in fixed split order
-//   3. W[r, c] = sum_j U[r, j] T[j, c]
-// Workspace: S * k * m floats of partials followed by k * m floats of T.
+// Weight projection W <- U (U^T W), generic path, two passes:
+//   1. T_s = U[rows of split s]^T W[rows of split s], float64
+//   2. W[r, c] = sum_j U[r, j] (sum_s T_s[j, c]), the splits in fixed order
+// Workspace: the splits' T_s as k x m float64 each (what the size formula, made
+// for float32 sums of 256 rows and their total, leaves room for).
 // ---------------------------------------------------------------------------
 
 constexpr int kGenericRowsPerSplit = 256;
 
-inline int64_t generic_splits(int64_t d) {
-  int64_t s = ceil_div(d, kGenericRowsPerSplit);
-  return s > 64 ? 64 : s;
-}
-
 size_t project_workspace_generic(int64_t d, int64_t k, int64_t m) {
-  return static_cast<size_t>(generic_splits(d) + 1) * k * m * sizeof(float);
+  int64_t s = ceil_div(d, kGenericRowsPerSplit);
+  s = s > 64 ? 64 : s;
+  return static_cast<size_t>(s + 1) * k * m * sizeof(float);
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void project_partial_kernel(const float *__restrict__ Uf,
-                                                              int64_t d, int64_t k,
-                                                              const T *__restrict__ W, int64_t m,
-                                                              int64_t ldw, int64_t rows_per_split,
-                                                              float *__restrict__ Tp) {
-  const int64_t c = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (c >= m) return;
-  const int64_t s = blockIdx.y;
-  const int64_t r0 = s * rows_per_split;
-  const int64_t r1 = r0 + rows_per_split < d ? r0 + rows_per_split : d;
-  for (int64_t j0 = 0; j0 < k; j0 += 8) {
-    Dot2 acc[8];
-    const int jn = static_cast<int>(k - j0 < 8 ? k - j0 : 8);
-    for (int64_t r = r0; r < r1; ++r) {
-      const float w = to_f32(W[r * ldw + c]);
-      const float *ur = Uf + r * k + j0;
+// Pass 1.  A workgroup takes 64 columns of W, KT column tiles of U and a split
+// of the rows, which its waves share by units of 32: lane (g, n) holds
+// columns 4 n .. 4 n + 3 of rows 8 g .. 8 g + 7 of a unit (16 lanes read 64
+// contiguous elements of a row), each row giving one f64 MFMA per column and
+// column tile.  The waves' sums are added through LDS in wave order.  Bound by
+// the f64 matrix rate of the CUs the workspace's splits can fill.  d = 4096,
+// k = 40, two float32 matrices of 512 columns: 1522 us (vector ALU, compensated
+// float32 sums, three passes) -> 84 us, pass 1 21 and pass 2 22 of each matrix.
+//
+// ROWS: the left factor is not U but a d x k float64 matrix given by rows (the
+// subspace update's coefficients; d then counts tokens and W is the gradient).
+template <typename T, int KT, bool ROWS>
+__global__ __launch_bounds__(256) void project_t_f64_kernel(const f32x4 *__restrict__ kfrag,
+                                                            const double *__restrict__ left, int kt,
+                                                            int64_t d, int64_t k,
+                                                            const T *__restrict__ W, int64_t m,
+                                                            int64_t ldw, int units_per_split,
+                                                            double *__restrict__ Tp) {
+  __shared__ double red[4][4][64][4];  // [wave][column of the lane][lane][row of the tile]
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 4, n = lane & 15;
+  const int64_t cb = 64 * static_cast<int64_t>(blockIdx.x);
+  const int64_t c0 = cb + 4 * n;
+  const bool whole = c0 + 4 <= m;
+  const int t0 = static_cast<int>(blockIdx.z) * KT;
+  const int units = static_cast<int>((d + 31) / 32);
+  const int u0 = static_cast<int>(blockIdx.y) * units_per_split;
+  const int u1 = u0 + units_per_split < units ? u0 + units_per_split : units;
+  f64x4 acc[KT][4];
 #pragma unroll
-      for (int jj = 0; jj < 8; ++jj)
-        if (jj < jn) acc[jj].add_prod(ur[jj], w);
+  for (int t = 0; t < KT; ++t)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[t][q] = f64x4{0., 0., 0., 0.};
+  struct Unit {
+    Row4<T> w[8];
+  };
+  auto load = [&](Unit &v, int u) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      int64_t r = 32 * static_cast<int64_t>(u) + 8 * g + e;
+      r = r < d ? r : d - 1;  // U's fragments are zero past row d
+      const T *p = W + r * ldw;
+      if (whole) {
+        v.w[e].load(p + c0);
+      } else {  // the right edge: columns past m read the last one, not stored
+        T x[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) x[q] = p[c0 + q < m ? c0 + q : m - 1];
+        v.w[e].load(x);
+      }
     }
+  };
+  if (u0 + wave < u1) {
+    Unit cur, nxt;
+    load(cur, u0 + wave);
+    for (int u = u0 + wave; u < u1; u += 4) {
+      load(nxt, u + 4 < u1 ? u + 4 : u);  // past the end the unit repeats, unused
+      const bool part = 32 * static_cast<int64_t>(u) + 32 > d;  // rows past d: no inf x 0
 #pragma unroll
-    for (int jj = 0; jj < 8; ++jj)
-      if (jj < jn) Tp[(s * k + j0 + jj) * m + c] = acc[jj].value();
+      for (int h = 0; h < 2; ++h) {
+        f32x4 a[ROWS ? 1 : KT];
+        if constexpr (!ROWS) {
+#pragma unroll
+          for (int t = 0; t < KT; ++t) {
+            const int tt = t0 + t < kt ? t0 + t : kt - 1;  // tiles past the last are not stored
+            a[t] = kfrag[((static_cast<int64_t>(u) * kt + tt) * 2 + h) * 64 + lane];
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int64_t r = 32 * static_cast<int64_t>(u) + 8 * g + 4 * h + e;
+          const bool out = part && r >= d;
+          double av[KT];
+#pragma unroll
+          for (int t = 0; t < KT; ++t) {
+            if constexpr (ROWS) {
+              const int64_t j = 16 * (t0 + t) + n;
+              av[t] = out ? 0.0 : left[r * k + (j < k ? j : k - 1)];
+            } else {
+              av[t] = static_cast<double>(a[t][e]);
+            }
+          }
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const double b = out ? 0.0 : cur.w[4 * h + e].at(q);
+#pragma unroll
+            for (int t = 0; t < KT; ++t) acc[t][q] = mfma64(av[t], b, acc[t][q]);
+          }
+        }
+      }
+      cur = nxt;
+    }
+  }
+  // lane (g, n) of column q holds T[16 t + 4 i + g][cb + 4 n + q]
+#pragma unroll
+  for (int t = 0; t < KT; ++t) {
+    if (t > 0) __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) red[wave][q][lane][i] = acc[t][q][i];
+    __syncthreads();
+    for (int idx = threadIdx.x; idx < 16 * 64; idx += 256) {
+      const int jl = idx >> 6, cl = idx & 63;
+      const int64_t j = 16 * static_cast<int64_t>(t0 + t) + jl, c = cb + cl;
+      if (j >= k || c >= m) continue;
+      const int at = 16 * (jl & 3) + (cl >> 2), i = jl >> 2, q = cl & 3;
+      double v = red[0][q][at][i];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) v += red[w][q][at][i];
+      Tp[(static_cast<int64_t>(blockIdx.y) * k + j) * m + c] = v;
+    }
   }
 }
 
-__global__ __launch_bounds__(256) void project_reduce_kernel(const float *__restrict__ Tp,
-                                                             int64_t splits, int64_t km,
-                                                             float *__restrict__ T) {
-  const int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (idx >= km) return;
-  Dot2 acc;
-  for (int64_t s = 0; s < splits; ++s) acc.add(Tp[s * km + idx]);
-  T[idx] = acc.value();
+// Pass 2.  A workgroup takes 64 NT columns (16 NT per wave, whose T the wave
+// holds in float64) and a range of 16-row tiles, whose U fragments it copies
+// into LDS once.  Lane (g, n) gets W[16 r + 4 g + i][c0 + n]: 16 lanes store
+// consecutive elements of a row.  Summing the splits one column step at a time
+// (a chain of loads) instead of one split at a time cost 15 to 35 us.
+template <typename T, int KG, int NT>
+__global__ __launch_bounds__(256) void project_w_f64_kernel(const f32x4 *__restrict__ rfrag, int kt,
+                                                            int64_t d, int64_t k,
+                                                            const double *__restrict__ Tp,
+                                                            int splits, T *__restrict__ W,
+                                                            int64_t m, int64_t ldw,
+                                                            int tiles_per_wg) {
+  extern __shared__ f32x4 us[];  // [tile of the range][kt][lane]
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 4, n = lane & 15;
+  const int ntile = static_cast<int>((d + 15) / 16);
+  const int r0 = static_cast<int>(blockIdx.y) * tiles_per_wg;
+  const int r1 = r0 + tiles_per_wg < ntile ? r0 + tiles_per_wg : ntile;
+  for (int e = threadIdx.x; e < (r1 - r0) * kt * 64; e += 256)
+    us[e] = rfrag[static_cast<int64_t>(r0) * kt * 64 + e];
+  const int nsteps = static_cast<int>((k + 3) / 4);
+  int64_t col[NT];
+  double tb[NT][4 * KG];  // T[4 s + g][col] of step s
+#pragma unroll
+  for (int b = 0; b < NT; ++b) {
+    col[b] = (static_cast<int64_t>(blockIdx.x) * 4 + wave) * (16 * NT) + 16 * b + n;
+    const int64_t c = col[b] < m ? col[b] : m - 1;
+#pragma unroll
+    for (int st = 0; st < 4 * KG; ++st) tb[b][st] = 0.0;
+    for (int sp = 0; sp < splits; ++sp)  // a split's loads in flight together
+#pragma unroll
+      for (int st = 0; st < 4 * KG; ++st) {
+        const int64_t j = 4 * st + g;
+        const double v = Tp[(sp * k + (j < k ? j : k - 1)) * m + c];
+        tb[b][st] += j < k ? v : 0.0;
+      }
+  }
+  __syncthreads();
+  for (int r = r0; r < r1; ++r) {
+    f64x4 acc[NT];
+#pragma unroll
+    for (int b = 0; b < NT; ++b) acc[b] = f64x4{0., 0., 0., 0.};
+    const f32x4 *f = us + (r - r0) * kt * 64 + lane;
+#pragma unroll
+    for (int q = 0; q < KG; ++q) {
+      const f32x4 u = f[(q < kt ? q : kt - 1) * 64];  // groups past the last take no step below
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (4 * q + e < nsteps) {
+#pragma unroll
+          for (int b = 0; b < NT; ++b)
+            acc[b] = mfma64(static_cast<double>(u[e]), tb[b][4 * q + e], acc[b]);
+        }
+    }
+#pragma unroll
+    for (int b = 0; b < NT; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int64_t row = 16 * static_cast<int64_t>(r) + 4 * g + i;
+        if (row < d && col[b] < m) W[row * ldw + col[b]] = from_f64<T>(acc[b][i]);
+      }
+  }
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void project_expand_kernel(const float *__restrict__ Uf,
-                                                             int64_t k, const float *__restrict__ Tm,
-                                                             T *__restrict__ W, int64_t m,
-                                                             int64_t ldw, int64_t cblocks) {
-  // blockIdx.x = r * cblocks + (256-column block)
-  const int64_t r = blockIdx.x / cblocks;
-  const int64_t c = (blockIdx.x - r * cblocks) * 256 + threadIdx.x;
-  if (c >= m) return;
-  const float *ur = Uf + r * k;
-  Dot2 acc;
-  for (int64_t j = 0; j < k; ++j) acc.add_prod(ur[j], Tm[j * m + c]);
-  W[r * ldw + c] = from_f32<T>(acc.value());
+hipError_t project_f64(const PackLayout &L, const void *packed, T *W, int64_t m, int64_t ldw,
+                       void *ws, hipStream_t s) {
+  const char *base = static_cast<const char *>(packed);
+  const f32x4 *kf = reinterpret_cast<const f32x4 *>(base + L.off_kfrag32);
+  const f32x4 *rf = reinterpret_cast<const f32x4 *>(base + L.off_rfrag32);
+  double *Tp = static_cast<double *>(ws);
+  // row splits: about two workgroups a CU, as many as the workspace holds, at
+  // least a unit per wave
+  const int64_t units = ceil_div(L.d, 32), cblocks = ceil_div(m, 64);
+  const int64_t room =
+      static_cast<int64_t>(project_workspace_generic(L.d, L.k, m) / (8 * L.k * m));
+  const int kt1 = L.kt < 4 ? L.kt : 4;
+  const int64_t z = ceil_div(L.kt, kt1);
+  int64_t splits = ceil_div(512, cblocks * z);
+  splits = splits < room ? splits : room;
+  splits = splits < ceil_div(units, 4) ? splits : ceil_div(units, 4);
+  const int64_t ups = ceil_div(units, splits);
+  splits = ceil_div(units, ups);
+  const dim3 g1(static_cast<unsigned>(cblocks), static_cast<unsigned>(splits),
+                static_cast<unsigned>(z));
+  auto pass1 = [&](auto kt) {
+    project_t_f64_kernel<T, decltype(kt)::value, false><<<g1, 256, 0, s>>>(
+        kf, nullptr, L.kt, L.d, L.k, W, m, ldw, static_cast<int>(ups), Tp);
+  };
+  switch (kt1) {
+    case 1: pass1(std::integral_constant<int, 1>{}); break;
+    case 2: pass1(std::integral_constant<int, 2>{}); break;
+    case 3: pass1(std::integral_constant<int, 3>{}); break;
+    default: pass1(std::integral_constant<int, 4>{}); break;
+  }
+  auto pass2 = [&](auto kg, auto nt) {
+    constexpr int KG = decltype(kg)::value, NT = decltype(nt)::value;
+    // row ranges: about two workgroups a CU (each reads its columns' T again),
+    // as many tiles as 32 KiB hold
+    const int64_t tiles = ceil_div(L.d, 16), gx = ceil_div(m, 64 * NT);
+    int64_t per = ceil_div(tiles, ceil_div(512, gx));
+    per = per < 32 / L.kt ? per : 32 / L.kt;
+    const int64_t most = ceil_div(tiles, 65535);  // grid limit, d above 2 million
+    per = per < most ? most : per;
+    project_w_f64_kernel<T, KG, NT>
+        <<<dim3(static_cast<unsigned>(gx), static_cast<unsigned>(ceil_div(tiles, per))), 256,
+           static_cast<size_t>(per) * 1024 * L.kt, s>>>(rf, L.kt, L.d, L.k, Tp,
+                                                        static_cast<int>(splits), W, m, ldw,
+                                                        static_cast<int>(per));
+    return hipGetLastError();
+  };
+  const std::integral_constant<int, 2> two{};
+  switch (L.kt) {
+    case 1: return pass2(std::integral_constant<int, 1>{}, two);
+    case 2: return pass2(std::integral_constant<int, 2>{}, two);
+    case 3: return pass2(std::integral_constant<int, 3>{}, two);
+    case 4: return pass2(std::integral_constant<int, 4>{}, two);
+    case 5:
+    case 6: return pass2(std::integral_constant<int, 6>{}, two);
+    case 7:
+    case 8: return pass2(std::integral_constant<int, 8>{}, two);
+    default: return pass2(std::integral_constant<int, 16>{}, std::integral_constant<int, 1>{});
+  }
 }
 
 hipError_t launch_project_generic(const PackLayout &L, const void *packed, void *W, int64_t m,
                                   int64_t ldw, void *ws, hipStream_t s) {
-  const float *Uf = reinterpret_cast<const float *>(static_cast<const char *>(packed) + L.off_f32);
-  const int64_t S = generic_splits(L.d);
-  const int64_t rps = ceil_div(L.d, S);
-  float *Tp = static_cast<float *>(ws);
-  float *Tm = Tp + S * L.k * m;
-  dim3 g1(static_cast<unsigned>(ceil_div(m, 256)), static_cast<unsigned>(S));
-  const int64_t km = L.k * m;
-  dim3 g2(static_cast<unsigned>(ceil_div(km, 256)));
-  const int64_t cblocks = ceil_div(m, 256);
-  dim3 g3(static_cast<unsigned>(cblocks * L.d));
-  if (L.dt == 0) {
-    project_partial_kernel<float><<<g1, 256, 0, s>>>(Uf, L.d, L.k, static_cast<const float *>(W),
-                                                     m, ldw, rps, Tp);
-    project_reduce_kernel<<<g2, 256, 0, s>>>(Tp, S, km, Tm);
-    project_expand_kernel<float><<<g3, 256, 0, s>>>(Uf, L.k, Tm, static_cast<float *>(W), m, ldw,
-                                                    cblocks);
-  } else {
-    project_partial_kernel<bf16_t><<<g1, 256, 0, s>>>(Uf, L.d, L.k,
-                                                      static_cast<const bf16_t *>(W), m, ldw,
-                                                      rps, Tp);
-    project_reduce_kernel<<<g2, 256, 0, s>>>(Tp, S, km, Tm);
-    project_expand_kernel<bf16_t><<<g3, 256, 0, s>>>(Uf, L.k, Tm, static_cast<bf16_t *>(W), m,
-                                                     ldw, cblocks);
+  return L.dt == 0 ? project_f64(L, packed, static_cast<float *>(W), m, ldw, ws, s)
+                   : project_f64(L, packed, static_cast<bf16_t *>(W), m, ldw, ws, s);
+}
+
+// ---------------------------------------------------------------------------
+// The subspace update's generic path: float64 coefficients G U, the loss
+// sum (g - c U^T)^2 taken directly, and the token contraction G^T (G U).
+// ---------------------------------------------------------------------------
+
+hipError_t launch_gen_coeffs(const PackLayout &L, const void *packed, const void *G, int64_t N,
+                             int64_t ldg, double *C64, hipStream_t s) {
+  return compress_f64<false>(L, packed, G, N, ldg, IdArgs{}, ProjArgs{}, kGenF64, C64, L.k, s);
+}
+
+// Workgroups of gen_loss_kernel: 64 tokens x a range of columns, about four a CU.
+GenLossGrid gen_loss_grid(int64_t N, int64_t d) {
+  GenLossGrid g;
+  g.tgroups = ceil_div(N > 0 ? N : 1, 64);
+  const int64_t pairs = ceil_div(d, 32);
+  g.per = ceil_div(pairs, ceil_div(1024, g.tgroups));
+  g.cols = ceil_div(pairs, g.per);
+  return g;
+}
+
+// part[workgroup] = the sum over its tokens and columns of (c U^T - g)^2: the
+// decompress's chain started at -g, its results squared and added in a fixed
+// order.
+template <typename T, int KG>
+__global__ __launch_bounds__(256) void gen_loss_kernel(const f32x4 *__restrict__ rfrag, int kt,
+                                                       int64_t d, int64_t k,
+                                                       const double *__restrict__ C64,
+                                                       const T *__restrict__ G, int64_t N,
+                                                       int64_t ldg, int64_t tgroups,
+                                                       int pairs_per_wg,
+                                                       double *__restrict__ part) {
+  __shared__ double red[256];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 4, n = lane & 15;
+  const int64_t tg = blockIdx.x % tgroups;
+  const int ntile = static_cast<int>((d + 15) / 16);
+  const int r0 = 2 * static_cast<int>(blockIdx.x / tgroups) * pairs_per_wg;
+  const int r1 = r0 + 2 * pairs_per_wg < ntile ? r0 + 2 * pairs_per_wg : ntile;
+  const int64_t i = 16 * (tg * 4 + wave) + n;
+  const bool live = i < N;
+  const int64_t ic = live ? i : N - 1;
+  const int nsteps = static_cast<int>((k + 3) / 4);
+  double cb[4 * KG];
+#pragma unroll
+  for (int st = 0; st < 4 * KG; ++st) {
+    const int64_t j = 4 * st + g;
+    cb[st] = j < k ? C64[ic * k + j] : 0.0;
   }
-  return hipGetLastError();
+  const T *gr = G + ic * ldg;
+  double l = 0.0;
+  for (int r = r0; r < r1; ++r) {
+    const int64_t c = 16 * static_cast<int64_t>(r) + 4 * g;
+    f64x4 acc = {0., 0., 0., 0.};
+    if (c + 4 <= d) {
+      Row4<T> v;
+      v.load(gr + c);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[q] = -v.at(q);
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (c + q < d) acc[q] = -static_cast<double>(to_f32(gr[c + q]));
+    }
+#pragma unroll
+    for (int q = 0; q < KG; ++q) {
+      const f32x4 u = rfrag[(static_cast<int64_t>(r) * kt + (q < kt ? q : kt - 1)) * 64 + lane];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (4 * q + e < nsteps)
+          acc = mfma64(static_cast<double>(u[e]), cb[4 * q + e], acc);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) l += acc[q] * acc[q];  // U's rows past d are zero, and so is acc
+  }
+  red[threadIdx.x] = live ? l : 0.0;
+  __syncthreads();
+  for (int w = 128; w >= 1; w >>= 1) {
+    if (static_cast<int>(threadIdx.x) < w) red[threadIdx.x] += red[threadIdx.x + w];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+}
+
+template <typename T>
+hipError_t gen_loss(const PackLayout &L, const void *packed, const T *G, int64_t N, int64_t ldg,
+                    const double *C64, double *part, hipStream_t s) {
+  const f32x4 *rf =
+      reinterpret_cast<const f32x4 *>(static_cast<const char *>(packed) + L.off_rfrag32);
+  const GenLossGrid gg = gen_loss_grid(N, L.d);
+  auto go = [&](auto kg) {
+    gen_loss_kernel<T, decltype(kg)::value>
+        <<<dim3(static_cast<unsigned>(gg.tgroups * gg.cols)), 256, 0, s>>>(
+            rf, L.kt, L.d, L.k, C64, G, N, ldg, gg.tgroups, static_cast<int>(gg.per), part);
+    return hipGetLastError();
+  };
+  switch (L.kt) {  // k <= kGrassMaxK
+    case 1: return go(std::integral_constant<int, 1>{});
+    case 2: return go(std::integral_constant<int, 2>{});
+    case 3: return go(std::integral_constant<int, 3>{});
+    case 4: return go(std::integral_constant<int, 4>{});
+    case 5:
+    case 6: return go(std::integral_constant<int, 6>{});
+    default: return go(std::integral_constant<int, 8>{});
+  }
+}
+
+hipError_t launch_gen_loss(const PackLayout &L, const void *packed, const void *G, int64_t N,
+                           int64_t ldg, const double *C64, double *part, hipStream_t s) {
+  return L.dt == 0
+             ? gen_loss(L, packed, static_cast<const float *>(G), N, ldg, C64, part, s)
+             : gen_loss(L, packed, static_cast<const bf16_t *>(G), N, ldg, C64, part, s);
+}
+
+// Token splits of the contraction: about two workgroups a CU, at least four
+// units of 32 tokens each.
+int64_t gen_token_splits(int64_t N, int64_t d, int64_t k) {
+  const int64_t units = ceil_div(N > 0 ? N : 1, 32);
+  const int64_t z = ceil_div(ceil_div(k, 16), 4);
+  int64_t sp = ceil_div(512, ceil_div(d, 64) * z);
+  sp = sp < ceil_div(units, 4) ? sp : ceil_div(units, 4);
+  return ceil_div(units, ceil_div(units, sp));
+}
+
+template <typename T>
+hipError_t gen_tokens(const PackLayout &L, const T *G, int64_t N, int64_t ldg, const double *C64,
+                      double *Tp, hipStream_t s) {
+  const int64_t units = ceil_div(N, 32), splits = gen_token_splits(N, L.d, L.k);
+  const int kt1 = L.kt < 4 ? L.kt : 4;
+  const dim3 grid(static_cast<unsigned>(ceil_div(L.d, 64)), static_cast<unsigned>(splits),
+                  static_cast<unsigned>(ceil_div(L.kt, kt1)));
+  const int ups = static_cast<int>(ceil_div(units, splits));
+  auto go = [&](auto kt) {
+    project_t_f64_kernel<T, decltype(kt)::value, true>
+        <<<grid, 256, 0, s>>>(nullptr, C64, L.kt, N, L.k, G, L.d, ldg, ups, Tp);
+    return hipGetLastError();
+  };
+  switch (kt1) {
+    case 1: return go(std::integral_constant<int, 1>{});
+    case 2: return go(std::integral_constant<int, 2>{});
+    case 3: return go(std::integral_constant<int, 3>{});
+    default: return go(std::integral_constant<int, 4>{});
+  }
+}
+
+hipError_t launch_gen_tokens(const PackLayout &L, const void *G, int64_t N, int64_t ldg,
+                             const double *C64, double *Tp, hipStream_t s) {
+  return L.dt == 0 ? gen_tokens(L, static_cast<const float *>(G), N, ldg, C64, Tp, s)
+                   : gen_tokens(L, static_cast<const bf16_t *>(G), N, ldg, C64, Tp, s);
 }
 
 }  // namespace sn

@@ -205,6 +205,21 @@ hipError_t launch_grass_tokens_mfma(const void *frag, int ktb, int64_t npad, con
                                     int64_t N, int64_t ldg, int64_t d, int64_t rows, int ds,
                                     int64_t m_pad, float *Tp, hipStream_t s);
 
+// Generic path (any shape and dtype, k <= kGrassMaxK), all float64: C64 = G U
+// (N x k); the loss sum (g - c U^T)^2 per workgroup into part; the token
+// contraction's splits Tp[split][j][i] = sum over its tokens of C64[n, j] G[n, i].
+struct GenLossGrid {
+  int64_t tgroups, cols, per;  // workgroups tgroups x cols, column pairs per workgroup
+};
+GenLossGrid gen_loss_grid(int64_t N, int64_t d);
+int64_t gen_token_splits(int64_t N, int64_t d, int64_t k);
+hipError_t launch_gen_coeffs(const PackLayout &L, const void *packed, const void *G, int64_t N,
+                             int64_t ldg, double *C64, hipStream_t s);
+hipError_t launch_gen_loss(const PackLayout &L, const void *packed, const void *G, int64_t N,
+                           int64_t ldg, const double *C64, double *part, hipStream_t s);
+hipError_t launch_gen_tokens(const PackLayout &L, const void *G, int64_t N, int64_t ldg,
+                             const double *C64, double *Tp, hipStream_t s);
+
 constexpr size_t kGrassStateHead = 256;  // bytes before Y in the accumulator state
 constexpr int kGrassMaxK = 128;          // largest k of the subspace update
 size_t grass_state_bytes(int64_t d, int64_t k);

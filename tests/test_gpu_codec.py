@@ -394,6 +394,53 @@ def test_generic_kernel_edges(dtype, d, k, n, pad, tables):
             assert np.all(np.abs(host(got) - ref) <= tol), what
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d,k,m,pad", [(7, 3, 5, 0), (31, 4, 64, 1), (33, 17, 65, 3), (161, 33, 1, 0),
+                                       (600, 70, 130, 1), (1000, 129, 67, 5), (300, 256, 40, 0)])
+def test_generic_weights_edges(dtype, d, k, m, pad):
+    """The float64 weight projection at the edges of its tiles: rows around a
+    unit of 32, part-filled column tiles of U (one to several per workgroup),
+    column blocks of W and row tiles, odd row strides.  float32: T and the
+    result are float64 sums rounded once (2^-24), 2^-22 of max(|value|,
+    column rms)."""
+    log(f"[generic weights] {dtype} d={d} k={k} m={m} pad={pad}")
+    st, o, _, _ = _small(d, k, m, dtype=dtype, seed=d + k + m)
+    basis = sn.sn_basis_pack(dev(st["U"], dtype))
+    buf = torch.full((d, m + pad), float("nan"), device="cuda",
+                     dtype=torch.bfloat16 if dtype == "bf16" else torch.float32)
+    W = buf[:, :m]
+    W.copy_(dev(st["G"], dtype).T)
+    sn.sn_project_weights(basis, W)
+    ref = oracle.project_weights(o["G"].T, o["U"]).T
+    assert_parity(host(W).T, oracle.round_to(ref, dtype), dtype, "project_weights")
+    assert bool(torch.isnan(buf[:, m:]).all())
+    if dtype == "f32":
+        tol = 2.0 ** -22 * np.maximum(np.abs(ref), np.sqrt(np.mean(ref * ref, -1, keepdims=True)))
+        assert np.all(np.abs(host(W).T - ref) <= tol)
+
+
+@pytest.mark.parametrize("dtype,d,k,n", [("f32", 7, 3, 1), ("f32", 33, 17, 65), ("f32", 130, 70, 31),
+                                         ("f32", 300, 128, 1000), ("bf16", 100, 20, 129)])
+def test_generic_subspace_edges(dtype, d, k, n):
+    """The float64 subspace accumulation at the edges of its tiles (tokens
+    around 32 and 64, part-filled column tiles and pairs): everything is
+    float64, so the loss and Y agree to 1e-12 of their terms."""
+    log(f"[generic subspace] {dtype} d={d} k={k} n={n}")
+    st, o, _, _ = _small(d, k, n, dtype=dtype, seed=d + k + n)
+    basis = sn.sn_basis_pack(dev(st["U"], dtype))
+    G = dev(st["G"], dtype)
+    state = sn.sn_grassmann_state(basis)
+    for _ in range(2):
+        cg = sn.sn_grassmann_accumulate(basis, G, state, want_cg=True)
+    assert torch.equal(cg.float(), sn.sn_grad_compress(basis, G).float())
+    c64 = o["G"] @ o["U"]
+    loss = float(np.sum((o["G"] - c64 @ o["U"].T) ** 2))
+    sc = state.scalars().cpu().numpy()
+    assert abs(sc[0] - 2 * loss) <= 1e-12 * 2 * float(np.sum(o["G"] ** 2)) and sc[1] == sc[3] == 2
+    err = np.abs(state.Y().cpu().numpy() - 2 * o["G"].T @ c64)
+    assert np.all(err <= 1e-12 * 2 * (np.abs(o["G"]).T @ (np.abs(o["G"]) @ np.abs(o["U"]))))
+
+
 @pytest.mark.parametrize("tables", ["EP", "E", "P", ""])
 @pytest.mark.parametrize("d,k,n", [(32, 7, 5), (64, 16, 33), (96, 33, 1), (480, 40, 17), (544, 128, 100),
                                    (1056, 100, 31), (288, 20, 8200), (256, 65, 4096),
