@@ -40,6 +40,8 @@ namespace {
 // ---------------------------------------------------------------------------
 // plans
 // ---------------------------------------------------------------------------
+constexpr int kMaxTokenSplits = 8;
+
 struct AccPlan {
   bool mfma = false;
   int kt = 0;          // C32 row length kp = 16 kt
@@ -68,8 +70,14 @@ AccPlan acc_plan(const PackLayout &L, int64_t N, bool mfma) {
       P.nparts = 2;
       P.ktb = L.kt;
     }
-    int64_t ds = ceil_div(N, 4096);
-    ds = ds < 1 ? 1 : (ds > 8 ? 8 : ds);
+    // token splits: a workgroup for every CU (a column block is 16 lanes x 8
+    // or 4 columns), at most 4096 tokens in a float32 sum while splits last,
+    // at least 128 (2000 tokens, d = 4096, k = 40: one split of 32 workgroups
+    // 50 us for the call, eight 33; d = 512, k = 8, 20000 tokens 32.5 -> 27)
+    int64_t ds = ceil_div(256, ceil_div(L.d, 16 * grass_tokens_cols(P.ktb)));
+    if (ds < ceil_div(N, 4096)) ds = ceil_div(N, 4096);
+    if (ds > ceil_div(N, 128)) ds = ceil_div(N, 128);
+    ds = ds < 1 ? 1 : (ds > kMaxTokenSplits ? kMaxTokenSplits : ds);
     P.rows = ceil_div(ceil_div(N, ds), 128) * 128;
     if (P.rows < 128) P.rows = 128;  // N = 0: the plan is only sized
     P.ds = static_cast<int>(ceil_div(N > 0 ? N : 1, P.rows));
@@ -172,11 +180,26 @@ __global__ __launch_bounds__(256) void finish_kernel(const float *__restrict__ t
     const int64_t i = idx / k, j = idx - (idx / k) * k;
     const int64_t part_stride = static_cast<int64_t>(ds) * m_pad * kpb;
     double acc = 0.0;
-    for (int sp = 0; tg && sp < ds; ++sp) acc += tg[(sp * k + j) * d + i];
-    for (int sp = 0; !tg && sp < ds; ++sp) {
-      const float *row = tp + (sp * m_pad + i) * kpb;
-      acc += static_cast<double>(row[j]);
-      acc += static_cast<double>(nparts == 1 ? row[k + j] : row[part_stride + j]);
+    if (tg) {
+      for (int sp = 0; sp < ds; ++sp) acc += tg[(sp * k + j) * d + i];
+    } else {
+      // every split's values first (independent loads in flight together), then
+      // the sum in order; ds <= kMaxTokenSplits
+      const float *row = tp + i * kpb;
+      const int64_t lo = nparts == 1 ? k + j : part_stride + j;
+      float h[kMaxTokenSplits], l[kMaxTokenSplits];
+#pragma unroll
+      for (int sp = 0; sp < kMaxTokenSplits; ++sp) {
+        const float *r = row + (sp < ds ? sp : 0) * m_pad * kpb;
+        h[sp] = r[j];
+        l[sp] = r[lo];
+      }
+#pragma unroll
+      for (int sp = 0; sp < kMaxTokenSplits; ++sp)
+        if (sp < ds) {
+          acc += static_cast<double>(h[sp]);
+          acc += static_cast<double>(l[sp]);
+        }
     }
     state_y(state)[idx] += acc;
   }

@@ -117,17 +117,23 @@ constexpr bool p1_two_waves() { return !CLAMP && KT <= 3; }
 template <int KT, bool CLAMP = false, int CW = p1_cw<KT>()>
 __global__ __launch_bounds__(kBlock, (p1_two_waves<KT, CLAMP>() ? 2 : 1)) void project_pass1_kernel(
     const bf16_t *__restrict__ kfrag, int64_t d, ColSegs ws, int64_t rows_per_split,
-    int64_t m_pad, float *__restrict__ Tp, int64_t nrows = 0) {
+    int64_t m_pad, float *__restrict__ Tp, int64_t nrows = 0, int split_x = 0) {
   constexpr int W32 = CW / 2;  // 32-bit words per lane and row
   typedef typename P1Vec<CW>::T vec;
   __shared__ f32x4 red[KT][CW][64];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, n = lane & 15;
-  const int64_t cb = static_cast<int64_t>(blockIdx.x) * (16 * CW);
-  // CLAMP (the token contraction) takes the splits last-first: the rows the
-  // preceding pass read last are the likeliest still to be cached
-  const int split = CLAMP ? static_cast<int>(gridDim.y - 1 - blockIdx.y) : blockIdx.y;
+  // CLAMP (the token contraction): with eight splits they lie along x, so an
+  // XCD takes one split's tokens and its L2 holds their operand (with the
+  // column blocks along x every XCD reads the whole operand: 54.5 -> 51 us at
+  // d = 4096, k = 40, 32768 tokens; with four splits it cost 3).  Splits go
+  // last-first: the rows the preceding pass read last are the likeliest still
+  // to be cached.
+  const int64_t cb = static_cast<int64_t>(CLAMP && split_x ? blockIdx.y : blockIdx.x) * (16 * CW);
+  const int split = !CLAMP ? static_cast<int>(blockIdx.y)
+                    : split_x ? static_cast<int>(gridDim.x - 1 - blockIdx.x)
+                              : static_cast<int>(gridDim.y - 1 - blockIdx.y);
   // the column segment holding this block (blocks never straddle two)
   int sg = 0;
   while (sg + 1 < ws.n && cb >= ws.c0[sg + 1]) ++sg;
@@ -450,10 +456,14 @@ template <int KT>
 void launch_p1_tokens(const bf16_t *frag, int64_t npad, const bf16_t *G, int64_t N, int64_t ldg,
                       int64_t d, int64_t rows, int ds, int64_t m_pad, float *Tp, hipStream_t s) {
   constexpr int CW = tok_cw<KT>();
-  dim3 grid(static_cast<unsigned>(ceil_div(d, 16 * CW)), static_cast<unsigned>(ds));
+  const unsigned blocks = static_cast<unsigned>(ceil_div(d, 16 * CW));
+  const int split_x = ds == 8;
+  const dim3 grid = split_x ? dim3(8, blocks) : dim3(blocks, static_cast<unsigned>(ds));
   project_pass1_kernel<KT, true, CW><<<grid, kBlock, 0, s>>>(frag, npad, one_seg(G, d, ldg),
-                                                              rows, m_pad, Tp, N);
+                                                              rows, m_pad, Tp, N, split_x);
 }
+
+int grass_tokens_cols(int ktb) { return ktb <= 5 ? tok_cw<1>() : tok_cw<kMfmaMaxKT>(); }
 
 hipError_t launch_grass_tokens_mfma(const void *frag, int ktb, int64_t npad, const void *G,
                                     int64_t N, int64_t ldg, int64_t d, int64_t rows, int ds,
