@@ -36,7 +36,7 @@ constexpr int kCols = 8;      // columns per thread
 constexpr int kStdCT = 256, kStdRG = 1, kStdR = 4;  // standard step
 constexpr int kSubCT = 64, kSubRG = 4, kSubR = 8;   // subspace step (32-row blocks)
 constexpr int kSubRows = kSubRG * kSubR;            // rows per column-sum block
-constexpr int kAlphaBlock = 128;
+constexpr int kAlphaWaves = 8;
 
 struct AdamArgs {
   float b1, omb1, b2, omb2;   // beta1, 1 - beta1, beta2, 1 - beta2
@@ -187,17 +187,26 @@ __global__ __launch_bounds__(CT * RG) void moments_kernel(T *__restrict__ W, int
   }
 }
 
-// Pass 2: alpha_c = 1 / (sqrt(sum_blocks colsum / (rows (1 - b2^t))) + eps),
-// the row blocks added in a fixed order in float64.
-__global__ __launch_bounds__(kAlphaBlock) void alpha_kernel(const float *__restrict__ colsum,
-                                                       int64_t nblk, int64_t rows, int64_t cols,
-                                                       double inv_bc2, double eps,
-                                                       float *__restrict__ alpha) {
-  const int64_t c = static_cast<int64_t>(blockIdx.x) * kAlphaBlock + threadIdx.x;
-  if (c >= cols) return;
+// Pass 2: alpha_c = 1 / (sqrt(sum_blocks colsum / (rows (1 - b2^t))) + eps), the
+// row blocks added in float64: wave w of a workgroup the blocks w, w + 8, ...
+// of its 64 columns, then the waves in order.  One thread per column left a
+// chain of 128 loads on 112 workgroups: 11.9 -> 4.8 us at 4096 x 14336.
+__global__ __launch_bounds__(64 * kAlphaWaves) void alpha_kernel(
+    const float *__restrict__ colsum, int64_t nblk, int64_t rows, int64_t cols, double inv_bc2,
+    double eps, float *__restrict__ alpha) {
+  __shared__ double red[kAlphaWaves][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t c = static_cast<int64_t>(blockIdx.x) * 64 + lane;
   double s = 0.0;
-#pragma unroll 4
-  for (int64_t b = 0; b < nblk; ++b) s += static_cast<double>(colsum[b * cols + c]);
+  if (c < cols) {
+#pragma unroll 8
+    for (int64_t b = w; b < nblk; b += kAlphaWaves) s += static_cast<double>(colsum[b * cols + c]);
+  }
+  red[w][lane] = s;
+  __syncthreads();
+  if (w != 0 || c >= cols) return;
+#pragma unroll
+  for (int i = 1; i < kAlphaWaves; ++i) s += red[i][lane];
   const double nu = s * inv_bc2 / static_cast<double>(rows);
   alpha[c] = static_cast<float>(1.0 / (sqrt(nu) + eps));
 }
@@ -259,7 +268,7 @@ hipError_t launch_t(void *Wv, int64_t ldw, const void *Gv, int64_t ldg, float *M
   float *alpha = colsum + static_cast<int64_t>(grid.y) * cols;
   moments_kernel<T, VEC, true, kSubCT, kSubRG, kSubR><<<grid, kSubCT * kSubRG, 0, s>>>(
       W, ldw, G, ldg, M, V, ldm, rows, cols, a, colsum);
-  alpha_kernel<<<dim3(static_cast<unsigned>(ceil_div(cols, kAlphaBlock))), kAlphaBlock, 0, s>>>(
+  alpha_kernel<<<dim3(static_cast<unsigned>(ceil_div(cols, 64))), 64 * kAlphaWaves, 0, s>>>(
       colsum, grid.y, rows, cols, inv_bc2, eps, alpha);
   apply_kernel<T, VEC, kSubCT, kSubRG, kSubR><<<grid, kSubCT * kSubRG, 0, s>>>(
       W, ldw, G, ldg, M, ldm, rows, cols, a, alpha);
