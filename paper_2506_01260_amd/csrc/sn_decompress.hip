@@ -158,7 +158,7 @@ template <int KS, bool HE, bool HP, int CM, bool PS>
 __global__ __launch_bounds__(kDThreads) void decompress_cb_kernel(
     const bf16_t *__restrict__ rfrag, int64_t d, int64_t k, const bf16_t *__restrict__ C,
     int64_t ldc, DTiling tm, IdArgs ids, ColSegs xs, int ncb, int ntiles,
-    int tiles_per_wg, int young_from) {
+    int tiles_per_wg, int young_from, int c_by_id) {
   constexpr int FR = 2 * KS;  // fragments per row group
   __shared__ u32x4 us[kPG * FR * 64];
   constexpr bool kIds = HE || HP;
@@ -254,7 +254,6 @@ __global__ __launch_bounds__(kDThreads) void decompress_cb_kernel(
     const unsigned T = tile_of(j);
     const int t0 = dtile_token0(tm, T);  // the tile's first token, once per tile
     auto tok_of = [&](int r) { return t0 + r < tm.N ? t0 + r : tm.N - 1; };
-    load_coeffs<KS, CM>(dt, tok_of(n), C, ldc, k, g);
     // Tiles are loaded in order 0, 1, 2, ...: every fourth tile the entries
     // move down one, so tile j's ids are always in entry 0 (a wave-uniform
     // branch and register moves; a choice among the entries by j / 4 would be
@@ -265,6 +264,11 @@ __global__ __launch_bounds__(kDThreads) void decompress_cb_kernel(
       e0 = e1; e1 = e2; e2 = e3;
       q0 = q1; q1 = q2; q2 = q3;
     }
+    // the coefficient row of token n: its own, or its id's (c_by_id)
+    int crow = tok_of(n);
+    if constexpr (HE)
+      if (c_by_id) crow = __builtin_amdgcn_ds_bpermute((16 * (j & 3) + n) * 4, e0);
+    load_coeffs<KS, CM>(dt, crow, C, ldc, k, g);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int r = 4 * i + q;
@@ -417,7 +421,8 @@ Slots resident_slots(K kernel) {
 
 template <int KS, bool HE, bool HP, int CM, bool PS = false>
 void launch_dcb(const bf16_t *rf, const PackLayout &L, const void *C, int64_t ldc,
-                const DTiling &tm, const IdArgs &ids, const ColSegs &X, hipStream_t s) {
+                const DTiling &tm, const IdArgs &ids, const ColSegs &X, int by_id,
+                hipStream_t s) {
   const int ncb = static_cast<int>(ceil_div(L.d, kDCols));
   // position-major tiles cover whole [batch, seq] sequences (the last one may
   // be short: its missing rows are read but not stored)
@@ -435,12 +440,13 @@ void launch_dcb(const bf16_t *rf, const PackLayout &L, const void *C, int64_t ld
   const int64_t young_from = tgroups * ncb > sl.cus ? sl.cus : tgroups * ncb;
   decompress_cb_kernel<KS, HE, HP, CM, PS><<<grid, kDThreads, 0, s>>>(
       rf, L.d, L.k, static_cast<const bf16_t *>(C), ldc, tm, ids, X, ncb,
-      static_cast<int>(ntiles), static_cast<int>(per), static_cast<int>(young_from));
+      static_cast<int>(ntiles), static_cast<int>(per), static_cast<int>(young_from), by_id);
 }
 
 template <int KS, int CM>
 void launch_dcb_t(const bf16_t *rf, const PackLayout &L, const void *C, int64_t ldc,
-                  const DTiling &tm, const IdArgs &ids, const ColSegs &X, hipStream_t s) {
+                  const DTiling &tm, const IdArgs &ids, const ColSegs &X, int by_id,
+                  hipStream_t s) {
   const bool he = ids.E != nullptr, hp = ids.P != nullptr;
   // Each P row piece is read once per call.  Beside T_fixed, a large P
   // (over 64 MiB) streams through the caches and evicts the T_fixed rows that
@@ -448,26 +454,27 @@ void launch_dcb_t(const bf16_t *rf, const PackLayout &L, const void *C, int64_t 
   // 32768 tokens).  Alone, or when small, it is loaded normally and stays in
   // the 256 MB Infinity Cache from one call to the next.
   if (he && hp && ids.n_pos * L.d * 2 > (int64_t{64} << 20))
-    launch_dcb<KS, true, true, CM, true>(rf, L, C, ldc, tm, ids, X, s);
+    launch_dcb<KS, true, true, CM, true>(rf, L, C, ldc, tm, ids, X, by_id, s);
   else if (he && hp)
-    launch_dcb<KS, true, true, CM>(rf, L, C, ldc, tm, ids, X, s);
+    launch_dcb<KS, true, true, CM>(rf, L, C, ldc, tm, ids, X, by_id, s);
   else if (he)
-    launch_dcb<KS, true, false, CM>(rf, L, C, ldc, tm, ids, X, s);
+    launch_dcb<KS, true, false, CM>(rf, L, C, ldc, tm, ids, X, by_id, s);
   else if (hp)
-    launch_dcb<KS, false, true, CM>(rf, L, C, ldc, tm, ids, X, s);
+    launch_dcb<KS, false, true, CM>(rf, L, C, ldc, tm, ids, X, by_id, s);
   else
-    launch_dcb<KS, false, false, CM>(rf, L, C, ldc, tm, ids, X, s);
+    launch_dcb<KS, false, false, CM>(rf, L, C, ldc, tm, ids, X, by_id, s);
 }
 
 template <int KS>
 void launch_dcb_ks(const bf16_t *rf, const PackLayout &L, const void *C, int64_t ldc, int cmode,
-                   const DTiling &tm, const IdArgs &ids, const ColSegs &X, hipStream_t s) {
+                   const DTiling &tm, const IdArgs &ids, const ColSegs &X, int by_id,
+                   hipStream_t s) {
   if (cmode == 0)
-    launch_dcb_t<KS, 0>(rf, L, C, ldc, tm, ids, X, s);
+    launch_dcb_t<KS, 0>(rf, L, C, ldc, tm, ids, X, by_id, s);
   else if (cmode == 1)
-    launch_dcb_t<KS, 1>(rf, L, C, ldc, tm, ids, X, s);
+    launch_dcb_t<KS, 1>(rf, L, C, ldc, tm, ids, X, by_id, s);
   else
-    launch_dcb_t<KS, 2>(rf, L, C, ldc, tm, ids, X, s);
+    launch_dcb_t<KS, 2>(rf, L, C, ldc, tm, ids, X, by_id, s);
 }
 
 // Leading dimensions below 2^31 elements keep row x row-bytes products in
@@ -476,6 +483,11 @@ constexpr int64_t kMaxLd = int64_t{1} << 31;
 bool table_ok(const void *T, int64_t ld) {
   return !T || (aligned16(T) && ld % 8 == 0 && ld < kMaxLd);
 }
+
+// by_id: C's rows are indexed by token id (ids.E given) instead of by token.
+hipError_t decompress_segs(const PackLayout &L, const void *packed, const void *C, int64_t N,
+                           int64_t ldc, const IdArgs &ids, const ColSegs &X, int by_id,
+                           hipStream_t s);
 
 }  // namespace
 
@@ -490,9 +502,23 @@ hipError_t launch_decompress_mfma(const PackLayout &L, const void *packed, const
   return launch_decompress_mfma_segs(L, packed, C, N, ldc, ids, one_seg(X, L.d, ldx), s);
 }
 
+hipError_t launch_decompress_mfma_by_id(const PackLayout &L, const void *packed, const void *CS,
+                                        int64_t N, int64_t ldcs, const IdArgs &ids, void *X,
+                                        int64_t ldx, hipStream_t s) {
+  return decompress_segs(L, packed, CS, N, ldcs, ids, one_seg(X, L.d, ldx), 1, s);
+}
+
 hipError_t launch_decompress_mfma_segs(const PackLayout &L, const void *packed, const void *C,
                                        int64_t N, int64_t ldc, const IdArgs &ids,
                                        const ColSegs &X, hipStream_t s) {
+  return decompress_segs(L, packed, C, N, ldc, ids, X, 0, s);
+}
+
+namespace {
+
+hipError_t decompress_segs(const PackLayout &L, const void *packed, const void *C, int64_t N,
+                           int64_t ldc, const IdArgs &ids, const ColSegs &X, int by_id,
+                           hipStream_t s) {
   for (int i = 0; i < X.n; ++i)
     if (X.ld[i] % 8 != 0 || X.ld[i] >= kMaxLd) return hipErrorNotSupported;
   if (!table_ok(ids.E, ids.lde) || !table_ok(ids.P, ids.ldp)) return hipErrorNotSupported;
@@ -514,13 +540,14 @@ hipError_t launch_decompress_mfma_segs(const PackLayout &L, const void *packed, 
     tm.batch = static_cast<int>(ceil_div(N, ids.seq_len));
   }
   switch (L.ks) {
-    case 1: launch_dcb_ks<1>(rf, L, C, ldc, cmode, tm, ids, X, s); break;
-    case 2: launch_dcb_ks<2>(rf, L, C, ldc, cmode, tm, ids, X, s); break;
-    case 3: launch_dcb_ks<3>(rf, L, C, ldc, cmode, tm, ids, X, s); break;
-    case 4: launch_dcb_ks<4>(rf, L, C, ldc, cmode, tm, ids, X, s); break;
+    case 1: launch_dcb_ks<1>(rf, L, C, ldc, cmode, tm, ids, X, by_id, s); break;
+    case 2: launch_dcb_ks<2>(rf, L, C, ldc, cmode, tm, ids, X, by_id, s); break;
+    case 3: launch_dcb_ks<3>(rf, L, C, ldc, cmode, tm, ids, X, by_id, s); break;
+    case 4: launch_dcb_ks<4>(rf, L, C, ldc, cmode, tm, ids, X, by_id, s); break;
     default: return hipErrorNotSupported;
   }
   return hipGetLastError();
 }
 
+}  // namespace
 }  // namespace sn

@@ -116,6 +116,10 @@ bool decompress_mfma_ok(const PackLayout &L, void *X, int64_t ldx, const IdArgs 
 hipError_t launch_decompress_mfma(const PackLayout &L, const void *packed, const void *C,
                                   int64_t N, int64_t ldc, const IdArgs &ids, void *X,
                                   int64_t ldx, hipStream_t s);
+// the same with C = CS[tok] (CS: ids.vocab rows; ids.E given)
+hipError_t launch_decompress_mfma_by_id(const PackLayout &L, const void *packed, const void *CS,
+                                        int64_t N, int64_t ldcs, const IdArgs &ids, void *X,
+                                        int64_t ldx, hipStream_t s);
 // the same with X given as column segments (each width a multiple of 256)
 hipError_t launch_decompress_mfma_segs(const PackLayout &L, const void *packed, const void *C,
                                        int64_t N, int64_t ldc, const IdArgs &ids,
