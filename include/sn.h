@@ -142,8 +142,9 @@ int32_t sn_decompress(const void *basis, int64_t d, int64_t k, int32_t dt,
 /* update (Sec. 4.5), so the projected tables T_fixed U (vocab x k) and P U   */
 /* (n_pos x k) can be built once per basis and every compress then streams X  */
 /* alone instead of also gathering two d-wide rows per token.  The result     */
-/* differs from sn_compress only by rounding: the tables are fp32 and the two */
-/* subtractions are rounded to fp32 after the product.                        */
+/* differs from sn_compress only by rounding: the tables are fp32, and on the */
+/* bf16 matrix-core path the two subtractions are rounded to fp32 after the   */
+/* product.                                                                   */
 /* ------------------------------------------------------------------------ */
 
 /* Bytes of the projected-table buffer for rank k, vocab token rows and n_pos
