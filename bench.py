@@ -416,8 +416,9 @@ def trace_summary(trace_dir: str, bench_log: str):
     e2 = e + 2 * pair
     e3 = e2 + 2 * max(5, K // 2)  # the cold pairs
 
-    def is_build(i):  # the table build: the compress kernel with the fp32-row epilogue
-        return names[i].startswith("compress_kernel<") and names[i].endswith(", 2>")
+    def is_build(i):  # the table build: a compress kernel with the fp32-row epilogue
+        return names[i].startswith(("compress_kernel<", "compress_split_kernel<")) and \
+            names[i].endswith(", 2>")
 
     proj = OP_KERNELS["compress_projected"][0]
     p0 = next((i for i in range(e3, len(rows)) if proj in rows[i]["Kernel_Name"]), None)
