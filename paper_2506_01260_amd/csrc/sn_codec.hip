@@ -1011,16 +1011,6 @@ bool split_preferred(const PackLayout &L, int64_t N) {
   return ceil_div(N, 16) <= static_cast<int64_t>(device_cus()) * (L.kt <= 4 ? 2 : 1);
 }
 
-// The subspace update's compress has no register-ring form, so where d is no
-// multiple of 64 the few-token kernel takes it at every N.
-bool grass_split(const PackLayout &L, int64_t N) {
-  return split_preferred(L, N) || L.d % kStageCols != 0;
-}
-
-bool grass_writes_wire(const PackLayout &L, int64_t N) {
-  return grass_split(L, N) == split_preferred(L, N);
-}
-
 hipError_t launch_compress(const PackLayout &L, const void *packed, const void *X, int64_t N,
                            int64_t ldx, const IdArgs &ids, void *C, int64_t ldc, hipStream_t s) {
   if (!stream_mfma_ok(L, X, ldx) || !tables_ok(ids))
@@ -1051,7 +1041,7 @@ hipError_t launch_compress_projected(const PackLayout &L, const void *packed, co
 }
 
 int64_t grass_compress_groups(const PackLayout &L, int64_t N, int64_t *steps) {
-  if (grass_split(L, N)) {  // two workgroups of 16 tokens per step
+  if (split_preferred(L, N)) {  // two workgroups of 16 tokens per step
     if (steps) *steps = ceil_div(N, 32);
     return 2 * ceil_div(N, 32);
   }
@@ -1075,8 +1065,8 @@ int64_t grass_compress_groups(const PackLayout &L, int64_t N, int64_t *steps) {
 hipError_t launch_grass_compress_mfma(const PackLayout &L, const void *packed, const void *G,
                                       int64_t N, int64_t ldg, const GrassOut &go, void *Cwire,
                                       int64_t ldc, hipStream_t s) {
-  if (!L.mfma) return hipErrorNotSupported;
-  if (grass_split(L, N))
+  if (!L.mfma || L.d % kStageCols != 0) return hipErrorNotSupported;
+  if (split_preferred(L, N))
     return launch_grass_compress_split(L, packed, G, N, ldg, go, Cwire, ldc, s);
   const bf16_t *kf =
       reinterpret_cast<const bf16_t *>(static_cast<const char *>(packed) + L.off_kfrag);

@@ -14,7 +14,7 @@
 // which is exact for any stored U; with D = U^T U - I (a section of the
 // packed basis) the row term is |g|^2 - |c|^2 + c D c^T.
 //
-// MFMA path (bf16, d a multiple of 32, k <= 128), per accumulate:
+// MFMA path (bf16, d a multiple of 64, k <= 128), per accumulate:
 //   1. the gradient compress's kernel with the subspace-update epilogue: per row
 //      |g|^2 (summed with the stages), c = g U, and the loss term (c D c^T
 //      on the matrix cores), summed per workgroup; C split into bf16 hi + lo
@@ -24,8 +24,8 @@
 //      Tp[split][i][j] = sum over the split's rows of C_hi/lo[n, j] G[n, i];
 //   3. finish_kernel: Y += the splits and halves in a fixed order (float64),
 //      the loss partials into the state's scalars.
-// Generic path (fp32, other shapes): the same three steps in float64 on the
-// f64 matrix cores, the loss taken directly as sum (g - c U^T)^2.  2048 tokens,
+// Generic path (fp32, other shapes and strides): the same three steps in float64
+// on the f64 matrix cores, the loss taken directly as sum (g - c U^T)^2.  2048 tokens,
 // d = 1024, k = 20, float32: 3211 -> 36 us (one thread per output before).
 //
 // Step (float64 throughout): Z = U^T Y, A = U + (2 eta / K)(Y - U Z), then
@@ -393,13 +393,19 @@ size_t grass_state_bytes(int64_t d, int64_t k) {
   return kGrassStateHead + align256(static_cast<size_t>(d) * k * 8);
 }
 
+// Whether the basis has an MFMA path.  d a multiple of 32 but not of 64 stays in
+// float64: the state's Y and loss are float64, and the MFMA path's fp32
+// coefficients and cancelling loss form would show in them (2^-17 of Y's terms
+// and 1e-5 of |g|^2 against 1e-12).
+bool grass_mfma_basis(const PackLayout &L) { return L.mfma && L.d % 64 == 0; }
+
 bool grass_mfma_ok(const PackLayout &L, const void *G, int64_t ldg) {
-  return L.mfma && aligned16(G) && ldg % 8 == 0;
+  return grass_mfma_basis(L) && aligned16(G) && ldg % 8 == 0;
 }
 
 size_t grass_workspace_bytes(const PackLayout &L, int64_t N) {
   size_t w = acc_plan(L, N, false).total;
-  if (L.mfma) {
+  if (grass_mfma_basis(L)) {
     const size_t m = acc_plan(L, N, true).total;
     w = m > w ? m : w;
   }
@@ -437,14 +443,8 @@ hipError_t launch_grass_accumulate(const PackLayout &L, const void *packed, cons
     go.npad = P.npad;
     int64_t steps = 0;
     const int64_t nlblk = grass_compress_groups(L, N, &steps);
-    const bool wire = grass_writes_wire(L, N);
-    hipError_t e =
-        launch_grass_compress_mfma(L, packed, G, N, ldg, go, wire ? Cwire : nullptr, ldc, s);
+    hipError_t e = launch_grass_compress_mfma(L, packed, G, N, ldg, go, Cwire, ldc, s);
     if (e != hipSuccess) return e;
-    if (Cwire && !wire) {
-      e = launch_compress(L, packed, G, N, ldg, IdArgs{}, Cwire, ldc, s);
-      if (e != hipSuccess) return e;
-    }
     if (with_su && steps < P.npad / 32) {
       const int64_t per_part = (P.npad / 32) * P.ktb * 512;  // bf16 per operand
       const int64_t tail = (P.npad / 32 - steps) * P.ktb * 512 / 4;  // as doubles

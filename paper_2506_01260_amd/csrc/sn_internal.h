@@ -197,9 +197,6 @@ hipError_t launch_grass_compress_mfma(const PackLayout &L, const void *packed, c
 hipError_t launch_grass_compress_split(const PackLayout &L, const void *packed, const void *G,
                                        int64_t N, int64_t ldg, const GrassOut &go, void *Cwire,
                                        int64_t ldc, hipStream_t s);
-// Whether launch_grass_compress_mfma's wire coefficients are the gradient
-// compress's bit for bit (the same kernel's sums).
-bool grass_writes_wire(const PackLayout &L, int64_t N);
 // Workgroups (loss partials) of that compress for N rows, and 32-row steps
 // of the operand it writes.
 int64_t grass_compress_groups(const PackLayout &L, int64_t N, int64_t *steps);

@@ -441,6 +441,28 @@ def test_generic_subspace_edges(dtype, d, k, n):
     assert np.all(err <= 1e-12 * 2 * (np.abs(o["G"]).T @ (np.abs(o["G"]) @ np.abs(o["U"]))))
 
 
+@pytest.mark.parametrize("d,k,n,pad", [(96, 8, 77, 0), (544, 128, 100, 0), (1056, 100, 31, 0),
+                                       (288, 20, 4200, 0), (320, 20, 300, 3), (512, 70, 129, 4)])
+def test_subspace_state_in_float64(d, k, n, pad):
+    """bf16 accumulations off the bf16 matrix-core path keep float64 throughout:
+    widths that are multiples of 32 but not of 64, and rows that are not 16-byte
+    aligned on a basis that has that path.  The loss and Y agree to 1e-12 of
+    their terms."""
+    log(f"[subspace float64] d={d} k={k} n={n} pad={pad}")
+    st, o, _, _ = _small(d, k, n, dtype="bf16", seed=d + k + n)
+    basis = sn.sn_basis_pack(dev(st["U"], "bf16"))
+    G = torch.full((n, d + pad), float("nan"), dtype=torch.bfloat16, device="cuda")[:, :d]
+    G.copy_(dev(st["G"], "bf16"))
+    state = sn.sn_grassmann_state(basis)
+    cg = sn.sn_grassmann_accumulate(basis, G, state, want_cg=True)
+    assert torch.equal(cg.view(torch.int16), sn.sn_grad_compress(basis, G).view(torch.int16))
+    c64 = o["G"] @ o["U"]
+    loss = float(np.sum((o["G"] - c64 @ o["U"].T) ** 2))
+    assert abs(float(state.scalars()[0]) - loss) <= 1e-12 * float(np.sum(o["G"] ** 2))
+    err = np.abs(state.Y().cpu().numpy() - o["G"].T @ c64)
+    assert np.all(err <= 1e-12 * (np.abs(o["G"]).T @ (np.abs(o["G"]) @ np.abs(o["U"]))))
+
+
 @pytest.mark.parametrize("tables", ["EP", "E", "P", ""])
 @pytest.mark.parametrize("d,k,n", [(32, 7, 5), (64, 16, 33), (96, 33, 1), (480, 40, 17), (544, 128, 100),
                                    (1056, 100, 31), (288, 20, 8200), (256, 65, 4096),

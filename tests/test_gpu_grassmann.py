@@ -91,7 +91,7 @@ def _check_y_chunked(state, Gf, U, K, chunk=256):
 
 
 SHAPES = [  # dtype, d, k, n: generic fp32; MFMA [C_hi | C_lo] with ragged n;
-            # MFMA with two operands (2k > 128); generic bf16 (d not a multiple of 64)
+            # MFMA with two operands (2k > 128); generic bf16 (d = 96, not a multiple of 64)
     ("f32", 256, 8, 512), ("bf16", 512, 40, 1000), ("bf16", 320, 20, 300),
     ("bf16", 512, 70, 700), ("bf16", 96, 8, 77), ("bf16", 1024, 128, 129),
     # one split per 128 tokens and its last part-filled; two splits with a
