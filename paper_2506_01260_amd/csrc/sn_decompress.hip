@@ -5,10 +5,11 @@
 // 16-token tiles; consecutive workgroups take consecutive token runs of the
 // same column block.  The block's slice of U (rfrag layout, 8 row groups of
 // 32 columns) is copied into LDS once and stays there, so the main loop has
-// no barriers: every wave walks its own tiles.  A width that is no multiple of
-// 256 (d >= 256, a multiple of 32) takes the same path, its last block
-// overlapping its neighbour: 4999 tokens, d = 1600, k = 16, both tables
-// 11.4 us, against 25 in the generic kernel, which takes what is left.
+// no barriers: every wave walks its own tiles.  Widths are multiples of 256;
+// the others keep the generic kernel's float64 sums (with the last block
+// overlapping its neighbour this kernel took 11.4 us against 25 at 4999 tokens,
+// d = 1600, k = 16, both tables, but in fp32 sums where they had been
+// compensated ones).
 //
 // Per tile and 128-column chunk a wave
 //  1. runs 4 row groups x 2 x ceil(k/32) MFMAs (A = U fragment from LDS,
@@ -156,9 +157,9 @@ struct DSmem {
 // PS: load the P rows with non-temporal loads (each is read once per call).
 template <int KS, bool HE, bool HP, int CM, bool PS>
 __global__ __launch_bounds__(kDThreads) void decompress_cb_kernel(
-    const bf16_t *__restrict__ rfrag, int64_t d, int64_t k, const bf16_t *__restrict__ C,
-    int64_t ldc, DTiling tm, IdArgs ids, ColSegs xs, int ncb, int ntiles,
-    int tiles_per_wg, int young_from, int c_by_id) {
+    const bf16_t *__restrict__ rfrag, int64_t k, const bf16_t *__restrict__ C, int64_t ldc,
+    DTiling tm, IdArgs ids, ColSegs xs, int ncb, int ntiles, int tiles_per_wg, int young_from,
+    int c_by_id) {
   constexpr int FR = 2 * KS;  // fragments per row group
   __shared__ u32x4 us[kPG * FR * 64];
   constexpr bool kIds = HE || HP;
@@ -171,11 +172,6 @@ __global__ __launch_bounds__(kDThreads) void decompress_cb_kernel(
   // columns of ncb / 8 blocks, of U, T_fixed and P alike.
   const int cb = static_cast<int>(blockIdx.x % static_cast<unsigned>(ncb));
   const int tg = static_cast<int>(blockIdx.x / static_cast<unsigned>(ncb));
-  // First column: when d is no multiple of 256 the last block reaches back into
-  // its neighbour, and the columns both hold are written twice with the same
-  // values.
-  const int64_t col0 = static_cast<int64_t>(cb + 1) * kDCols <= d ? static_cast<int64_t>(cb) * kDCols
-                                                                 : d - kDCols;
   const int g = lane >> 4, n = lane & 15;  // MFMA layout
   const int q = lane >> 4, m = lane & 15;  // row layout
 
@@ -233,17 +229,17 @@ __global__ __launch_bounds__(kDThreads) void decompress_cb_kernel(
     }
   }
   {  // the block's U slice -> LDS, 1 KiB per direct-to-LDS load
-    const bf16_t *src = rfrag + col0 / 32 * FR * 512;
+    const bf16_t *src = rfrag + static_cast<int64_t>(cb) * kPG * FR * 512;
     for (int f = wave; f < kPG * FR; f += kDW) lds_dma_16(src + f * 512 + lane * 8, us + f * 64);
     wait_vmcnt<0>();
   }
   __syncthreads();
   if (nt == 0) return;
 
-  const int64_t col_r = col0 + 8 * m;  // row-layout column
+  const int64_t col_r = static_cast<int64_t>(cb) * kDCols + 8 * m;  // row-layout column
   // the column segment of X that holds this block (blocks never straddle two)
   int sg = 0;
-  while (sg + 1 < xs.n && col0 >= xs.c0[sg + 1]) ++sg;
+  while (sg + 1 < xs.n && static_cast<int64_t>(cb) * kDCols >= xs.c0[sg + 1]) ++sg;
   // Row addresses are base + row x row-bytes with both factors below 2^32
   // (the launch checks the leading dimensions): one 32 x 32 -> 64-bit
   // multiply-add per row, no 64-bit products.
@@ -423,7 +419,7 @@ template <int KS, bool HE, bool HP, int CM, bool PS = false>
 void launch_dcb(const bf16_t *rf, const PackLayout &L, const void *C, int64_t ldc,
                 const DTiling &tm, const IdArgs &ids, const ColSegs &X, int by_id,
                 hipStream_t s) {
-  const int ncb = static_cast<int>(ceil_div(L.d, kDCols));
+  const int ncb = static_cast<int>(L.d / kDCols);
   // position-major tiles cover whole [batch, seq] sequences (the last one may
   // be short: its missing rows are read but not stored)
   const int64_t ntiles = tm.batch > 0 ? static_cast<int64_t>(tm.batch) * (tm.seq / 16)
@@ -439,7 +435,7 @@ void launch_dcb(const bf16_t *rf, const PackLayout &L, const void *C, int64_t ld
   // workgroups past the first one per CU (when the grid has more)
   const int64_t young_from = tgroups * ncb > sl.cus ? sl.cus : tgroups * ncb;
   decompress_cb_kernel<KS, HE, HP, CM, PS><<<grid, kDThreads, 0, s>>>(
-      rf, L.d, L.k, static_cast<const bf16_t *>(C), ldc, tm, ids, X, ncb,
+      rf, L.k, static_cast<const bf16_t *>(C), ldc, tm, ids, X, ncb,
       static_cast<int>(ntiles), static_cast<int>(per), static_cast<int>(young_from), by_id);
 }
 
@@ -492,7 +488,7 @@ hipError_t decompress_segs(const PackLayout &L, const void *packed, const void *
 }  // namespace
 
 bool decompress_mfma_ok(const PackLayout &L, void *X, int64_t ldx, const IdArgs &ids) {
-  return L.mfma && L.d >= kDCols && aligned16(X) && ldx % 8 == 0 && ldx < kMaxLd &&
+  return L.mfma && L.d % kDCols == 0 && aligned16(X) && ldx % 8 == 0 && ldx < kMaxLd &&
          table_ok(ids.E, ids.lde) && table_ok(ids.P, ids.ldp);
 }
 

@@ -441,6 +441,30 @@ def test_generic_subspace_edges(dtype, d, k, n):
     assert np.all(err <= 1e-12 * 2 * (np.abs(o["G"]).T @ (np.abs(o["G"]) @ np.abs(o["U"]))))
 
 
+@pytest.mark.parametrize("d,n", [(288, 20), (1600, 300), (416, 9000)])
+def test_recovery_keeps_cancelling_sums_off_multiples_of_256(d, n):
+    """bf16 recovery of widths that are multiples of 32 but not of 256 adds the
+    tables to C U^T before the one rounding, in more than fp32: with a product of
+    2^30 that the tables cancel, the small rest survives.  Whole numbers, so the
+    results are exact."""
+    log(f"[recovery, cancelling] d={d} n={n}")
+    k, V = 16, 50
+    g = np.random.default_rng(d)
+    U, C = np.zeros((d, k), np.float32), np.zeros((n, k), np.float32)
+    U[:, 0], U[:, 3] = 2.0 ** 15, g.integers(1, 100, d)
+    C[:, 0], C[:, 3] = 2.0 ** 15, 1.0
+    basis = sn.sn_basis_pack(dev(synth.store(U, "bf16"), "bf16"))
+    table = lambda v: torch.full((V, d), v, dtype=torch.bfloat16, device="cuda")  # noqa: E731
+    tok, Cd = ids(g.integers(0, V, n)), dev(synth.store(C, "bf16"), "bf16")
+    for E, P in ((table(-2.0 ** 30), None), (None, table(-2.0 ** 30)),
+                 (table(-2.0 ** 29), table(-2.0 ** 29))):
+        X = sn.sn_decompress(basis, Cd, tok=tok, E=E, P=P, seq_len=V)
+        assert np.array_equal(host(X), np.broadcast_to(U[:, 3].astype(np.float64), (n, d)))
+    CS = Cd[:1].expand(V, k).contiguous()
+    X = sn.sn_embed_lowrank_forward(basis, CS, tok, E=table(-2.0 ** 30))
+    assert np.array_equal(host(X), np.broadcast_to(U[:, 3].astype(np.float64), (n, d)))
+
+
 @pytest.mark.parametrize("d,k,n,pad", [(96, 8, 77, 0), (544, 128, 100, 0), (1056, 100, 31, 0),
                                        (288, 20, 4200, 0), (320, 20, 300, 3), (512, 70, 129, 4)])
 def test_subspace_state_in_float64(d, k, n, pad):
@@ -471,8 +495,7 @@ def test_few_token_compress_and_narrow_blocks(d, k, n, tables):
     """The few-token compress: fewer units of 64 columns than waves, an odd last
     step of 32, part-filled token tiles, every column-tile count class, and the
     token counts on both sides of its dispatch (one and two rounds of
-    workgroups); the decompress of widths that are no multiple of 256 (the
-    last column block overlaps its neighbour).  The wire coefficients of the
+    workgroups); the decompress of widths around multiples of 256.  The wire coefficients of the
     subspace update stay those of the gradient compress."""
     log(f"[few tokens] d={d} k={k} n={n} tables={tables!r}")
     st, o, tok, pos = _small(d, min(k, d), n, dtype="bf16", seed=d + k + n)
