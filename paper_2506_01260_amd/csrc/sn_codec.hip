@@ -1013,10 +1013,13 @@ bool split_preferred(const PackLayout &L, int64_t N) {
 
 hipError_t launch_compress(const PackLayout &L, const void *packed, const void *X, int64_t N,
                            int64_t ldx, const IdArgs &ids, void *C, int64_t ldc, hipStream_t s) {
-  if (!stream_mfma_ok(L, X, ldx) || !tables_ok(ids))
+  // With tables the bf16 kernels take whole stages of 64 columns only: the other
+  // widths' X - P - T_fixed is summed in float64 (the three products in fp32
+  // lose the rest where large embeddings cancel).
+  if (!stream_mfma_ok(L, X, ldx) ||
+      ((ids.E || ids.P) && (L.d % kStageCols != 0 || !tables_ok(ids))))
     return launch_compress_generic(L, packed, X, N, ldx, ids, C, ldc, s);
-  // with tables compress_kernel takes whole stages of 64 columns only
-  if (split_preferred(L, N) || ((ids.E || ids.P) && L.d % kStageCols != 0))
+  if (split_preferred(L, N))
     return launch_compress_split(L, packed, X, N, ldx, ids, C, ldc, s);
   return launch_compress_mfma(L, packed, X, N, ldx, ids, C, ldc, s);
 }

@@ -465,6 +465,31 @@ def test_recovery_keeps_cancelling_sums_off_multiples_of_256(d, n):
     assert np.array_equal(host(X), np.broadcast_to(U[:, 3].astype(np.float64), (n, d)))
 
 
+@pytest.mark.parametrize("d,n", [(96, 20), (1056, 300), (288, 9000)])
+def test_compress_keeps_cancelling_sums_off_multiples_of_64(d, n):
+    """bf16 compress with tables, widths that are multiples of 32 but not of 64:
+    an activation of 2^15 that the embeddings cancel exactly leaves the small
+    rest, in more than fp32.  Whole numbers, so the results are exact."""
+    log(f"[compress, cancelling] d={d} n={n}")
+    k, V = 16, 50
+    g = np.random.default_rng(d)
+    U, X = np.zeros((d, k), np.float32), np.zeros((n, d), np.float32)
+    U[0], U[5] = 2.0 ** 15, g.integers(1, 100, k)
+    X[:, 0], X[:, 5] = 2.0 ** 15, 1.0
+    basis = sn.sn_basis_pack(dev(synth.store(U, "bf16"), "bf16"))
+    tok, Xd = ids(g.integers(0, V, n)), dev(synth.store(X, "bf16"), "bf16")
+
+    def table(v):
+        t = np.zeros((V, d), np.float32)
+        t[:, 0] = v
+        return dev(synth.store(t, "bf16"), "bf16")
+
+    for E, P in ((table(2.0 ** 15), None), (None, table(2.0 ** 15)),
+                 (table(2.0 ** 14), table(2.0 ** 14))):
+        C = sn.sn_compress(basis, Xd, tok=tok, E=E, P=P, seq_len=V)
+        assert np.array_equal(host(C), np.broadcast_to(U[5].astype(np.float64), (n, k)))
+
+
 @pytest.mark.parametrize("d,k,n,pad", [(96, 8, 77, 0), (544, 128, 100, 0), (1056, 100, 31, 0),
                                        (288, 20, 4200, 0), (320, 20, 300, 3), (512, 70, 129, 4)])
 def test_subspace_state_in_float64(d, k, n, pad):
