@@ -1016,6 +1016,7 @@ GenLossGrid gen_loss_grid(int64_t N, int64_t d) {
   const int64_t pairs = ceil_div(d, 32);
   g.per = ceil_div(pairs, ceil_div(1024, g.tgroups));
   g.cols = ceil_div(pairs, g.per);
+  g.most = 1024 + g.tgroups;  // cols <= ceil(1024 / tgroups)
   return g;
 }
 
@@ -1115,11 +1116,12 @@ hipError_t launch_gen_loss(const PackLayout &L, const void *packed, const void *
 
 // Token splits of the contraction: about two workgroups a CU, at least four
 // units of 32 tokens each.
-int64_t gen_token_splits(int64_t N, int64_t d, int64_t k) {
+int64_t gen_token_splits(int64_t N, int64_t d, int64_t k, int64_t *most) {
   const int64_t units = ceil_div(N > 0 ? N : 1, 32);
   const int64_t z = ceil_div(ceil_div(k, 16), 4);
   int64_t sp = ceil_div(512, ceil_div(d, 64) * z);
   sp = sp < ceil_div(units, 4) ? sp : ceil_div(units, 4);
+  if (most) *most = sp;
   return ceil_div(units, ceil_div(units, sp));
 }
 

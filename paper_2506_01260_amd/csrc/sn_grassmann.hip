@@ -55,6 +55,9 @@ struct AccPlan {
   size_t off_c = 0, off_frag = 0, off_part = 0, off_tp = 0, total = 0;
 };
 
+// The sections are laid out for bounds that never fall as N grows, so a workspace
+// sized for the largest N serves every smaller one: the counts in use fall where
+// a split's tokens round up to 128 (1024 tokens in eight splits, 1025 in five).
 AccPlan acc_plan(const PackLayout &L, int64_t N, bool mfma) {
   AccPlan P;
   P.mfma = mfma;
@@ -84,19 +87,22 @@ AccPlan acc_plan(const PackLayout &L, int64_t N, bool mfma) {
     P.npad = P.ds * P.rows;
     P.m_pad = ceil_div(L.d, 128) * 128;
     P.off_frag = off;
-    off = align256(off + static_cast<size_t>(P.nparts) * (P.npad / 32) * P.ktb * 1024);
+    // npad < N + 128 ds
+    const int64_t steps = (N + 128 * kMaxTokenSplits) / 32;
+    off = align256(off + static_cast<size_t>(P.nparts) * steps * P.ktb * 1024);
     P.off_part = off;
     off = align256(off + static_cast<size_t>(P.nlblk) * 8);
     P.off_tp = off;
-    off = align256(off + static_cast<size_t>(P.nparts) * P.ds * P.m_pad * 16 * P.ktb * 4);
+    off = align256(off + static_cast<size_t>(P.nparts) * ds * P.m_pad * 16 * P.ktb * 4);
   } else {
     P.off_c = off;
     off = align256(off + static_cast<size_t>(N) * L.k * 8);
     P.off_part = off;
-    off = align256(off + static_cast<size_t>(P.nlblk) * 8);
-    P.ds = static_cast<int>(gen_token_splits(N, L.d, L.k));
+    off = align256(off + static_cast<size_t>(lg.most) * 8);
+    int64_t most = 0;
+    P.ds = static_cast<int>(gen_token_splits(N, L.d, L.k, &most));
     P.off_tp = off;
-    off = align256(off + static_cast<size_t>(P.ds) * L.d * L.k * 8);
+    off = align256(off + static_cast<size_t>(most) * L.d * L.k * 8);
   }
   P.total = off;
   return P;

@@ -211,11 +211,13 @@ hipError_t launch_grass_tokens_mfma(const void *frag, int ktb, int64_t npad, con
 // Generic path (any shape and dtype, k <= kGrassMaxK), all float64: C64 = G U
 // (N x k); the loss sum (g - c U^T)^2 per workgroup into part; the token
 // contraction's splits Tp[split][j][i] = sum over its tokens of C64[n, j] G[n, i].
+// (`most`: at least the count, and never falling as N grows.)
 struct GenLossGrid {
   int64_t tgroups, cols, per;  // workgroups tgroups x cols, column pairs per workgroup
+  int64_t most;
 };
 GenLossGrid gen_loss_grid(int64_t N, int64_t d);
-int64_t gen_token_splits(int64_t N, int64_t d, int64_t k);
+int64_t gen_token_splits(int64_t N, int64_t d, int64_t k, int64_t *most = nullptr);
 hipError_t launch_gen_coeffs(const PackLayout &L, const void *packed, const void *G, int64_t N,
                              int64_t ldg, double *C64, hipStream_t s);
 hipError_t launch_gen_loss(const PackLayout &L, const void *packed, const void *G, int64_t N,

@@ -50,6 +50,20 @@ def test_packed_and_workspace_sizes():
     assert sn.lib().sn_project_weights_workspace_bytes(4096, 40, 1, 4096) > 0
 
 
+@pytest.mark.parametrize("dt", [0, 1])
+@pytest.mark.parametrize("d,k", [(256, 3), (257, 5), (512, 8), (1024, 16), (1600, 16), (2048, 20),
+                                 (4096, 40), (4096, 128), (8192, 82)])
+def test_subspace_workspace_never_shrinks_with_more_tokens(d, k, dt):
+    """A workspace of the size for the largest N serves every smaller N (and the
+    step, N = 0): the reported size never falls as N grows."""
+    last, at = 0, 0
+    ns = list(range(0, 4400)) + [n + e for n in range(4416, 40000, 32) for e in (0, 1, 31)]
+    for n in ns:
+        need = sn.sn_grassmann_workspace_bytes(d, k, dt, n)
+        assert need >= last, f"{need} bytes for {n} tokens, {last} for {at}"
+        last, at = need, n
+
+
 def _compress(**over):
     a = dict(basis=FAKE, d=256, k=8, dt=1, X=FAKE + (1 << 20), N=16, ldx=256, tok=FAKE + (2 << 20),
              E=FAKE + (3 << 20), vocab=10, lde=256, pos=None, P=None, n_pos=0, ldp=0,
