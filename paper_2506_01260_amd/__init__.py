@@ -173,7 +173,9 @@ def _mat(t: torch.Tensor, name: str):
     if cols > 1 and t.stride(1) != 1:
         raise SnError(2, f"{name} must be row-major (unit column stride)")
     ld = t.stride(0) if rows > 1 else cols
-    return t.data_ptr(), rows, cols, max(ld, cols)
+    if ld < cols:  # rows that overlap (t.expand(n, cols)): no row stride says where they lie
+        raise SnError(2, f"{name}'s row stride {ld} is below its {cols} columns")
+    return t.data_ptr(), rows, cols, ld
 
 
 def _ids(t, name, n):

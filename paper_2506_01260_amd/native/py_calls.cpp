@@ -21,8 +21,6 @@
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
-#include <algorithm>
-
 #include "sn.h"
 
 namespace {
@@ -68,7 +66,8 @@ bool mat(PyObject *o, Mat &m) {
   m.rows = t->size(0);
   m.cols = t->size(1);
   if (m.cols > 1 && t->stride(1) != 1) return false;
-  m.ld = std::max(m.rows > 1 ? t->stride(0) : m.cols, m.cols);
+  m.ld = m.rows > 1 ? t->stride(0) : m.cols;
+  if (m.ld < m.cols) return false;
   m.type = t->scalar_type();
   m.p = t->data_ptr();
   return true;

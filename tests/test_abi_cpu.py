@@ -126,6 +126,34 @@ def test_decompress_and_projection_validation():
     assert L.sn_basis_pack(FAKE + (1 << 20), 256, 8, 4, 1, FAKE, 1 << 20, None) == 2
 
 
+class _Device:
+    """What the binding asks of a device matrix, with the strides of a CPU tensor."""
+    is_cuda, dtype = True, None
+
+    def __init__(self, t):
+        self.t = t
+
+    def __getattr__(self, name):
+        return getattr(self.t, name)
+
+
+def test_binding_rejects_overlapping_rows():
+    """A row stride below the width (one row expanded to many, a sliding window)
+    would be read past the storage as a matrix of whole rows: it is refused.  One
+    row, no row and wider strides are taken."""
+    import torch
+    row = torch.zeros(1, 64)
+    for bad in (row.expand(16, 64), torch.zeros(100).as_strided((10, 20), (4, 1))):
+        with pytest.raises(sn.SnError) as e:
+            sn._mat(_Device(bad), "X")
+        assert e.value.status == 2
+    assert sn._mat(_Device(row), "X")[1:] == (1, 64, 64)
+    assert sn._mat(_Device(row.expand(1, 64)), "X")[1:] == (1, 64, 64)
+    assert sn._mat(_Device(torch.zeros(0, 64)), "X")[1:] == (0, 64, 64)
+    assert sn._mat(_Device(torch.zeros(5, 70)[:, :64]), "X")[1:] == (5, 64, 70)
+    assert sn._mat(_Device(torch.zeros(5, 1)[:, :1]), "X")[1:] == (5, 1, 1)
+
+
 def test_binding_rejects_host_tensors():
     import torch
     U = torch.zeros(64, 8, dtype=torch.bfloat16)
