@@ -1001,14 +1001,31 @@ hipError_t launch_compress_projected_mfma(const PackLayout &L, const void *packe
   return launch_plain<kEpiProjected>(L, packed, X, N, ldx, pa, C, ldc, s);
 }
 
-// Whether the few-token kernel (one workgroup per 16 tokens) takes a compress
-// of N tokens: while its workgroups fit one round on the CUs, two rounds while
-// U is narrow (its re-reads grow with k).  d = 4096, k = 40, both tables: 4096
-// tokens 15 us against 37 in compress_kernel, 8192 tokens 33 / 37; d = 8192,
-// k = 82: 43 / 76 and 84 / 77; d = 4096, k = 40, no tables, 8192 tokens
-// 16 / 20; d = 2048, k = 20, 16384 tokens 17.6 / 14.4.
-bool split_preferred(const PackLayout &L, int64_t N) {
-  return ceil_div(N, 16) <= static_cast<int64_t>(device_cus()) * (L.kt <= 4 ? 2 : 1);
+// Whether the few-token kernel (one workgroup per 16 tokens) takes a compress of
+// N tokens with `tabs` gathered tables.
+//
+// One round of workgroups on the CUs: yes (d = 4096, k = 40, both tables, 4096
+// tokens 36.6 us in compress_kernel, 21.3 here; 1024 tokens 35.4 / 12.8), except
+// without tables where U is wide against the rows (d = 512, k = 128, 4096 tokens
+// 6.8 / 7.3; d = 256, k = 40 3.9 / 3.7).
+//
+// A second round doubles the time and reads U twice per CU while compress_kernel's
+// serial chain over d stays as it is, so it pays only where U is narrow or that
+// chain long, and the rows come from the Infinity Cache, as those just computed
+// do.  6000 tokens, compress_kernel / here:
+//   no tables    d = 2048, k = 8  9.9 / 7.6    k = 64 12.2 / 15.0
+//                d = 4096, k = 40 19.5 / 15.8  k = 64 21.5 / 20.3
+//                d = 3072, k = 64 17.2 / 18.6  d = 8192, k = 64 (98 MB) 40.1 / 46.7
+//   both tables  d = 1024, k = 10 11.2 / 10.8  d = 4096, k = 64 42.5 / 44.1
+// and with tables at 8192 tokens d = 2048, k = 20 20.5 / 24.0.
+bool split_preferred(const PackLayout &L, int64_t N, int tabs) {
+  const int64_t groups = ceil_div(N, 16), cus = device_cus();
+  if (groups <= cus) return tabs > 0 || L.d > 4 * L.k;
+  if (tabs == 0)
+    return groups <= 2 * cus &&
+           (L.kt == 1 || (L.kt <= 4 && L.d >= (L.kt == 4 ? 4096 : 3072) &&
+                          N * L.d <= (int64_t{36} << 20)));
+  return 2 * groups <= 3 * cus && L.kt <= 3 && L.d >= (L.kt == 1 ? 1024 : 3072);
 }
 
 hipError_t launch_compress(const PackLayout &L, const void *packed, const void *X, int64_t N,
@@ -1019,7 +1036,7 @@ hipError_t launch_compress(const PackLayout &L, const void *packed, const void *
   if (!stream_mfma_ok(L, X, ldx) ||
       ((ids.E || ids.P) && (L.d % kStageCols != 0 || !tables_ok(ids))))
     return launch_compress_generic(L, packed, X, N, ldx, ids, C, ldc, s);
-  if (split_preferred(L, N))
+  if (split_preferred(L, N, (ids.E != nullptr) + (ids.P != nullptr)))
     return launch_compress_split(L, packed, X, N, ldx, ids, C, ldc, s);
   return launch_compress_mfma(L, packed, X, N, ldx, ids, C, ldc, s);
 }
@@ -1028,7 +1045,7 @@ hipError_t launch_table_project(const PackLayout &L, const void *packed, const v
                                 int64_t rows, int64_t ldt, float *out, int64_t kp, hipStream_t s) {
   if (!stream_mfma_ok(L, T, ldt))
     return launch_table_project_generic(L, packed, T, rows, ldt, out, kp, s);
-  if (split_preferred(L, rows))
+  if (split_preferred(L, rows, 0))
     return launch_table_project_split(L, packed, T, rows, ldt, out, kp, s);
   return launch_table_project_mfma(L, packed, T, rows, ldt, out, kp, s);
 }
@@ -1038,13 +1055,13 @@ hipError_t launch_compress_projected(const PackLayout &L, const void *packed, co
                                      int64_t ldc, hipStream_t s) {
   if (!stream_mfma_ok(L, X, ldx))
     return launch_compress_projected_generic(L, packed, X, N, ldx, pa, C, ldc, s);
-  if (split_preferred(L, N))
+  if (split_preferred(L, N, 0))
     return launch_compress_projected_split(L, packed, X, N, ldx, pa, C, ldc, s);
   return launch_compress_projected_mfma(L, packed, X, N, ldx, pa, C, ldc, s);
 }
 
 int64_t grass_compress_groups(const PackLayout &L, int64_t N, int64_t *steps) {
-  if (split_preferred(L, N)) {  // two workgroups of 16 tokens per step
+  if (split_preferred(L, N, 0)) {  // two workgroups of 16 tokens per step
     if (steps) *steps = ceil_div(N, 32);
     return 2 * ceil_div(N, 32);
   }
@@ -1069,7 +1086,7 @@ hipError_t launch_grass_compress_mfma(const PackLayout &L, const void *packed, c
                                       int64_t N, int64_t ldg, const GrassOut &go, void *Cwire,
                                       int64_t ldc, hipStream_t s) {
   if (!L.mfma || L.d % kStageCols != 0) return hipErrorNotSupported;
-  if (split_preferred(L, N))
+  if (split_preferred(L, N, 0))
     return launch_grass_compress_split(L, packed, G, N, ldg, go, Cwire, ldc, s);
   const bf16_t *kf =
       reinterpret_cast<const bf16_t *>(static_cast<const char *>(packed) + L.off_kfrag);

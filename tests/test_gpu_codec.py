@@ -490,6 +490,28 @@ def test_compress_keeps_cancelling_sums_off_multiples_of_64(d, n):
         assert np.array_equal(host(C), np.broadcast_to(U[5].astype(np.float64), (n, k)))
 
 
+@pytest.mark.parametrize("d,k,n,tables", [
+    (256, 63, 50, ""), (256, 64, 50, ""), (256, 64, 50, "P"), (256, 16, 8192, ""), (256, 16, 8193, ""),
+    (256, 17, 4097, ""), (3072, 33, 4100, ""), (3072, 49, 4100, ""), (1024, 16, 6144, "EP"), (1024, 16, 6145, "EP"),
+    (960, 16, 4097, "E"), (3072, 48, 4097, "P"), (3072, 49, 4097, "P")])
+def test_compress_on_both_sides_of_the_few_token_rule(d, k, n, tables):
+    """Shapes on both sides of each line of the rule that picks the few-token
+    compress (at 256 CUs): the rank against the width and one round of
+    workgroups, a second round with and without tables."""
+    log(f"[few-token rule] d={d} k={k} n={n} tables={tables!r}")
+    st, o, tok, pos = _small(d, k, n, dtype="bf16", seed=d + k + n)
+    basis = sn.sn_basis_pack(dev(st["U"], "bf16"))
+    E, P = (dev(st[x], "bf16") if x in tables else None for x in "EP")
+    oE, oP = (o[x] if x in tables else None for x in "EP")
+    C = sn.sn_compress(basis, dev(st["X"], "bf16"), tok=ids(tok), E=E, P=P, pos=ids(pos))
+    ref = oracle.compress(o["X"], o["U"], tok, oE, oP, pos=pos)
+    assert_parity(host(C), oracle.round_to(ref, "bf16"), "bf16", "compress")
+    if tables == "":
+        G = dev(st["G"], "bf16")
+        cg = sn.sn_grassmann_accumulate(basis, G, sn.sn_grassmann_state(basis), want_cg=True)
+        assert torch.equal(cg.view(torch.int16), sn.sn_grad_compress(basis, G).view(torch.int16))
+
+
 @pytest.mark.parametrize("d,k,n,pad", [(96, 8, 77, 0), (544, 128, 100, 0), (1056, 100, 31, 0),
                                        (288, 20, 4200, 0), (320, 20, 300, 3), (512, 70, 129, 4)])
 def test_subspace_state_in_float64(d, k, n, pad):
