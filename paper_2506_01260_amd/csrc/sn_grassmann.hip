@@ -73,11 +73,14 @@ AccPlan acc_plan(const PackLayout &L, int64_t N, bool mfma) {
       P.nparts = 2;
       P.ktb = L.kt;
     }
-    // token splits: a workgroup for every CU (a column block is 16 lanes x 8
-    // or 4 columns), at most 4096 tokens in a float32 sum while splits last,
-    // at least 128 (2000 tokens, d = 4096, k = 40: one split of 32 workgroups
-    // 50 us for the call, eight 33; d = 512, k = 8, 20000 tokens 32.5 -> 27)
-    int64_t ds = ceil_div(256, ceil_div(L.d, 16 * grass_tokens_cols(P.ktb)));
+    // token splits: as many as fit one workgroup per CU (a column block is 16
+    // lanes x 8 or 4 columns), at most 4096 tokens in a float32 sum while splits
+    // last, at least 128 (2000 tokens, d = 4096, k = 40: one split of 32
+    // workgroups 50 us for the call, eight 33).  One split more, past one round of
+    // workgroups, loses what it should gain: d = 6144, k = 40, 8192 tokens in six
+    // splits of 48 workgroups 81 us, in five 71, in two 74; d = 5120, k = 82,
+    // 4352 tokens in four of 80 107, in three 91, in two 90.
+    int64_t ds = 256 / ceil_div(L.d, 16 * grass_tokens_cols(P.ktb));
     if (ds < ceil_div(N, 4096)) ds = ceil_div(N, 4096);
     if (ds > ceil_div(N, 128)) ds = ceil_div(N, 128);
     ds = ds < 1 ? 1 : (ds > kMaxTokenSplits ? kMaxTokenSplits : ds);

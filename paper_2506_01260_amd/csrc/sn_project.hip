@@ -124,10 +124,8 @@ __global__ __launch_bounds__(kBlock, (p1_two_waves<KT, CLAMP>() ? 2 : 1)) void p
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, n = lane & 15;
-  // CLAMP (the token contraction): with eight splits they lie along x, so an
-  // XCD takes one split's tokens and its L2 holds their operand (with the
-  // column blocks along x every XCD reads the whole operand: 54.5 -> 51 us at
-  // d = 4096, k = 40, 32768 tokens; with four splits it cost 3).  Splits go
+  // CLAMP (the token contraction): splits along x (launch_p1_tokens says when)
+  // give an XCD one split's tokens, whose operand its L2 then holds.  Splits go
   // last-first: the rows the preceding pass read last are the likeliest still
   // to be cached.
   const int64_t cb = static_cast<int64_t>(CLAMP && split_x ? blockIdx.y : blockIdx.x) * (16 * CW);
@@ -457,7 +455,12 @@ void launch_p1_tokens(const bf16_t *frag, int64_t npad, const bf16_t *G, int64_t
                       int64_t d, int64_t rows, int ds, int64_t m_pad, float *Tp, hipStream_t s) {
   constexpr int CW = tok_cw<KT>();
   const unsigned blocks = static_cast<unsigned>(ceil_div(d, 16 * CW));
-  const int split_x = ds == 8;
+  // Eight splits along x go to the eight XCDs; with the column blocks along x
+  // every XCD reads the whole operand.  d = 4096, k = 40 (32 blocks), 32768
+  // tokens: 54.5 -> 51 us; d = 3072, k = 41 (48 blocks) 114 -> 109 for the call.
+  // More blocks lose what the operand gains (k = 82: d = 4096, 64 blocks
+  // 210 -> 221, d = 8192 442 -> 462), and with four splits it cost 3.
+  const int split_x = ds == 8 && blocks <= 48;
   const dim3 grid = split_x ? dim3(8, blocks) : dim3(blocks, static_cast<unsigned>(ds));
   project_pass1_kernel<KT, true, CW><<<grid, kBlock, 0, s>>>(frag, npad, one_seg(G, d, ldg),
                                                               rows, m_pad, Tp, N, split_x);

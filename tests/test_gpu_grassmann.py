@@ -97,6 +97,9 @@ SHAPES = [  # dtype, d, k, n: generic fp32; MFMA [C_hi | C_lo] with ragged n;
     # one split per 128 tokens and its last part-filled; two splits with a
     # column block of 64; eight splits of more than 128
     ("bf16", 256, 40, 257), ("bf16", 8192, 70, 200), ("bf16", 2048, 20, 5000),
+    # six splits (40 column blocks); eight splits of more column blocks than the
+    # splits-along-x form takes
+    ("bf16", 5120, 20, 1500), ("bf16", 3584, 50, 29000),
 ]
 
 
