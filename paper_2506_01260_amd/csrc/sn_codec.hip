@@ -1017,14 +1017,18 @@ hipError_t launch_compress_projected_mfma(const PackLayout &L, const void *packe
 //                d = 4096, k = 40 19.5 / 15.8  k = 64 21.5 / 20.3
 //                d = 3072, k = 64 17.2 / 18.6  d = 8192, k = 64 (98 MB) 40.1 / 46.7
 //   both tables  d = 1024, k = 10 11.2 / 10.8  d = 4096, k = 64 42.5 / 44.1
-// and with tables at 8192 tokens d = 2048, k = 20 20.5 / 24.0.
+// and with tables at 8192 tokens d = 2048, k = 20 20.5 / 24.0.  The subspace
+// update's epilogue follows the rows (d = 6144, k = 64, 6000 tokens 73 / 78 us for
+// the accumulate).
 bool split_preferred(const PackLayout &L, int64_t N, int tabs) {
   const int64_t groups = ceil_div(N, 16), cus = device_cus();
   if (groups <= cus) return tabs > 0 || L.d > 4 * L.k;
-  if (tabs == 0)
+  if (tabs == 0) {
+    const bool wide = L.kt == 4;
     return groups <= 2 * cus &&
-           (L.kt == 1 || (L.kt <= 4 && L.d >= (L.kt == 4 ? 4096 : 3072) &&
-                          N * L.d <= (int64_t{36} << 20)));
+           (L.kt == 1 || (L.kt <= 4 && L.d >= (wide ? 4096 : 3072) &&
+                          N * L.d <= int64_t{wide ? 32 : 36} << 20));
+  }
   return 2 * groups <= 3 * cus && L.kt <= 3 && L.d >= (L.kt == 1 ? 1024 : 3072);
 }
 
