@@ -480,6 +480,15 @@ bool table_ok(const void *T, int64_t ld) {
   return !T || (aligned16(T) && ld % 8 == 0 && ld < kMaxLd);
 }
 
+// How coefficient rows may be read: 0 = 16-byte chunks, 1 = 4-byte pairs, 2 = bf16
+// by bf16.
+int coeff_mode(const void *C, int64_t ldc, int64_t k) {
+  const uintptr_t a = reinterpret_cast<uintptr_t>(C);
+  return (a & 15) == 0 && ldc % 8 == 0 && k % 8 == 0   ? 0
+         : (a & 3) == 0 && ldc % 2 == 0 && k % 2 == 0 ? 1
+                                                      : 2;
+}
+
 // by_id: C's rows are indexed by token id (ids.E given) instead of by token.
 hipError_t decompress_segs(const PackLayout &L, const void *packed, const void *C, int64_t N,
                            int64_t ldc, const IdArgs &ids, const ColSegs &X, int by_id,
@@ -496,6 +505,20 @@ hipError_t launch_decompress_mfma(const PackLayout &L, const void *packed, const
                                   int64_t N, int64_t ldc, const IdArgs &ids, void *X,
                                   int64_t ldx, hipStream_t s) {
   return launch_decompress_mfma_segs(L, packed, C, N, ldc, ids, one_seg(X, L.d, ldx), s);
+}
+
+// Each of the d / 256 column blocks gathers the C_S rows again, so reading them by
+// id costs the more the narrower the loads and the wider the rows, against a launch
+// and a pass over N x k.  16384 tokens, gathered first / by id, both tables:
+//   16-byte chunks  d = 512, k = 8 13.1 / 11.1 us   d = 8192, k = 128 148 / 141
+//   4-byte pairs    d = 4096, k = 126 1.06x         d = 5120, k = 126 121 / 127
+//   single values   d = 2048, k = 81 1.01x          d = 3072, k = 81 0.96x (32768)
+// Rows that the gather buffer lets the kernel read in wider loads are gathered:
+// d = 8192, k = 128, an odd stride 149 / 194.
+bool decompress_by_id_preferred(const PackLayout &L, const void *CS, int64_t N, int64_t ldcs) {
+  const int mode = coeff_mode(CS, ldcs, L.k);
+  if (mode > coeff_mode(nullptr, L.k, L.k)) return false;  // the buffer: aligned, stride k
+  return mode == 0 || N <= 4096 || L.d <= (mode == 1 ? 4096 : 2048);
 }
 
 hipError_t launch_decompress_mfma_by_id(const PackLayout &L, const void *packed, const void *CS,
@@ -520,11 +543,7 @@ hipError_t decompress_segs(const PackLayout &L, const void *packed, const void *
   if (!table_ok(ids.E, ids.lde) || !table_ok(ids.P, ids.ldp)) return hipErrorNotSupported;
   const bf16_t *rf =
       reinterpret_cast<const bf16_t *>(static_cast<const char *>(packed) + L.off_rfrag);
-  // how the coefficient rows may be read: 16-byte chunks, 4-byte pairs, or bf16 by bf16
-  const uintptr_t ca = reinterpret_cast<uintptr_t>(C);
-  const int cmode = (ca & 15) == 0 && ldc % 8 == 0 && L.k % 8 == 0   ? 0
-                    : (ca & 3) == 0 && ldc % 2 == 0 && L.k % 2 == 0 ? 1
-                                                                    : 2;
+  const int cmode = coeff_mode(C, ldc, L.k);
   DTiling tm{static_cast<int>(N), 0, 0};
   // position-major order for the default positions of [batch, seq] rows; a
   // short last sequence is allowed while the rows it lacks (read, not

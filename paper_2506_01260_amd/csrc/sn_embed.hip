@@ -4,8 +4,9 @@
 //
 // forward   X0[i] = P[pos_i] + T_fixed[tok_i] + C_S[tok_i] U^T: exactly Sec.
 //           4.3.1's recovery with C = C_S[tok].  The decompress kernel reads
-//           the C_S rows by token id where it has the ids (T_fixed given);
-//           else the rows are gathered into a coefficient buffer first.
+//           the C_S rows by token id where it has the ids (T_fixed given)
+//           and that is the faster form; else the rows are gathered into a
+//           coefficient buffer first.
 // backward  gC_S[v] += sum over i with tok_i = v of dX0[i] U: the gradient
 //           coefficients dX0 U in fp32 (the compress kernel's fp32-row
 //           epilogue), then a deterministic sum by token id in two kernels:
@@ -325,10 +326,11 @@ hipError_t launch_embed_forward(const PackLayout &L, const void *packed, const v
                                 int64_t vocab, int64_t ldcs, const int32_t *tok,
                                 const IdArgs &ids, int64_t N, void *X0, int64_t ldx, void *ws,
                                 hipStream_t s) {
-  // with T_fixed the decompress has every row's token id and reads the C_S rows
+  // with T_fixed the decompress has every row's token id and can read the C_S rows
   // itself (16384 tokens, d = 2048, k = 20: 2.9 + 17.8 us as two kernels,
   // 18.0 as one)
-  if (ids.E && decompress_mfma_ok(L, X0, ldx, ids))
+  if (ids.E && decompress_mfma_ok(L, X0, ldx, ids) &&
+      decompress_by_id_preferred(L, CS, N, ldcs))
     return launch_decompress_mfma_by_id(L, packed, CS, N, ldcs, ids, X0, ldx, s);
   const EmbedPlan P = embed_plan(L.k, L.dt, N, vocab, false);
   void *C = static_cast<char *>(ws) + P.off_c;

@@ -116,7 +116,9 @@ bool decompress_mfma_ok(const PackLayout &L, void *X, int64_t ldx, const IdArgs 
 hipError_t launch_decompress_mfma(const PackLayout &L, const void *packed, const void *C,
                                   int64_t N, int64_t ldc, const IdArgs &ids, void *X,
                                   int64_t ldx, hipStream_t s);
-// the same with C = CS[tok] (CS: ids.vocab rows; ids.E given)
+// the same with C = CS[tok] (CS: ids.vocab rows; ids.E given), and whether that is
+// faster than gathering the rows into a buffer of stride k first
+bool decompress_by_id_preferred(const PackLayout &L, const void *CS, int64_t N, int64_t ldcs);
 hipError_t launch_decompress_mfma_by_id(const PackLayout &L, const void *packed, const void *CS,
                                         int64_t N, int64_t ldcs, const IdArgs &ids, void *X,
                                         int64_t ldx, hipStream_t s);

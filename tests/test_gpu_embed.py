@@ -179,3 +179,62 @@ def test_out_of_range_ids_are_clamped_and_flagged():
                                  err_flag=flag)
     torch.cuda.synchronize()
     assert int(flag.item()) & 1
+
+
+def _forward_parts(dtype, d, k, vocab, n, seq, cs_pad=0, offset=0):
+    """Basis, tables, ids and C_S (row stride k + cs_pad, base offset elements past
+    an aligned address) of a forward, on the device and as float64."""
+    cfg = synth.Config("embed", dtype, d, k, vocab, 1, n, True, 0.0, 1e-2)
+    b, emb, idx, dec = _setup(cfg)
+    U, E, P = dec(b["U"]).astype(np.float64), dec(emb["E"]), dec(emb["P"])
+    CSs = synth.store(oracle.round_to(em.lowrank_init(E, U), dtype), dtype)
+    buf = torch.full((vocab * (k + cs_pad) + offset,), float("nan"), device="cuda",
+                     dtype=torch.bfloat16 if dtype == "bf16" else torch.float32)
+    CS = buf[offset:].view(vocab, k + cs_pad)[:, :k]
+    CS.copy_(dev(CSs, dtype))
+    return sn.sn_basis_pack(dev(b["U"], dtype)), U, E, P[:seq], dec(CSs), CS, idx["tok"], emb
+
+
+@pytest.mark.parametrize("d,k,vocab,n,seq,tables,cs_pad,offset", [
+    (256, 16, 500, 100, 50, "E", 0, 0), (512, 40, 900, 1000, 512, "EP", 8, 0),   # 16-byte chunks
+    (512, 20, 900, 8 * 512 - 17, 512, "EP", 0, 0),   # pairs; a short last sequence
+    (512, 40, 900, 700, 96, "EP", 2, 0), (512, 40, 900, 700, 96, "E", 1, 0),     # gathered first
+    (512, 40, 900, 700, 96, "EP", 0, 1),             # gathered: an odd base
+    (2048, 21, 300, 4100, 64, "EP", 0, 0), (2304, 21, 300, 4100, 64, "EP", 0, 0),  # single values
+    (4352, 22, 300, 4100, 64, "EP", 0, 0), (4352, 24, 300, 4100, 64, "EP", 0, 0)])
+def test_forward_by_id_and_gathered(d, k, vocab, n, seq, tables, cs_pad, offset):
+    """The forward on both sides of the rule that lets the decompress read C_S by
+    token id (loads of the rows, width, tokens), with T_fixed alone and with
+    default and explicit positions, against the oracle."""
+    log(f"[embed forward] by id d={d} k={k} n={n} tables={tables} pad={cs_pad} offset={offset}")
+    basis, U, E, P, CSf, CS, tok, emb = _forward_parts("bf16", d, k, vocab, n, seq, cs_pad, offset)
+    pos = (np.arange(n) * 7 % seq).astype(np.int32)
+    Ed = dev(emb["E"], "bf16")
+    Pd = dev(emb["P"], "bf16")[:seq] if "P" in tables else None
+    for explicit in (False, True) if "P" in tables else (False,):
+        where = dict(pos=ids(pos)) if explicit else dict(seq_len=seq)
+        got = sn.sn_embed_lowrank_forward(basis, CS, ids(tok), E=Ed, P=Pd, **where)
+        at = pos if explicit else np.arange(n) % seq
+        ref = E[tok].astype(np.float64) + CSf[tok].astype(np.float64) @ U.T
+        if "P" in tables:
+            ref = ref + P[at]
+        assert_parity(host(got), oracle.round_to(ref, "bf16"), "bf16", f"X0 explicit={explicit}")
+
+
+@pytest.mark.parametrize("cs_pad", [0, 1])
+def test_forward_out_of_range_ids_with_a_fixed_table(cs_pad):
+    """Ids out of range select the first or last row of T_fixed and of C_S alike and
+    are flagged, read by id (aligned C_S) and gathered first (odd row stride)."""
+    log(f"[embed forward] out-of-range ids with T_fixed, pad={cs_pad}")
+    d, k, vocab, n = 512, 40, 50, 200
+    basis, U, E, P, CSf, CS, tok, emb = _forward_parts("bf16", d, k, vocab, n, n, cs_pad)
+    bad = tok.copy()
+    bad[[3, 17, 70, 199]] = -2, vocab, 2 ** 31 - 1, -2 ** 31
+    flag = torch.zeros(1, dtype=torch.int32, device="cuda")
+    got = sn.sn_embed_lowrank_forward(basis, CS, ids(bad), E=dev(emb["E"], "bf16"),
+                                      P=dev(emb["P"], "bf16"), seq_len=n, err_flag=flag)
+    torch.cuda.synchronize()
+    assert int(flag.item()) == 1
+    use = np.clip(bad.astype(np.int64), 0, vocab - 1)
+    ref = P[:n] + E[use].astype(np.float64) + CSf[use].astype(np.float64) @ U.T
+    assert_parity(host(got), oracle.round_to(ref, "bf16"), "bf16", "X0")
