@@ -884,7 +884,9 @@ __global__ __launch_bounds__(256) void project_w_f64_kernel(const f32x4 *__restr
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, n = lane & 15;
   const int ntile = static_cast<int>((d + 15) / 16);
-  const int r0 = static_cast<int>(blockIdx.y) * tiles_per_wg;
+  const int64_t range = static_cast<int64_t>(blockIdx.z) * gridDim.y + blockIdx.y;
+  if (range * tiles_per_wg >= ntile) return;
+  const int r0 = static_cast<int>(range) * tiles_per_wg;
   const int r1 = r0 + tiles_per_wg < ntile ? r0 + tiles_per_wg : ntile;
   for (int e = threadIdx.x; e < (r1 - r0) * kt * 64; e += 256)
     us[e] = rfrag[static_cast<int64_t>(r0) * kt * 64 + e];
@@ -970,13 +972,12 @@ hipError_t project_f64(const PackLayout &L, const void *packed, T *W, int64_t m,
     const int64_t tiles = ceil_div(L.d, 16), gx = ceil_div(m, 64 * NT);
     int64_t per = ceil_div(tiles, ceil_div(512, gx));
     per = per < 32 / L.kt ? per : 32 / L.kt;
-    const int64_t most = ceil_div(tiles, 65535);  // grid limit, d above 2 million
-    per = per < most ? most : per;
+    const int64_t ranges = ceil_div(tiles, per), gy = ranges < 32768 ? ranges : 32768;
+    const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(gy),
+                    static_cast<unsigned>(ceil_div(ranges, gy)));
     project_w_f64_kernel<T, KG, NT>
-        <<<dim3(static_cast<unsigned>(gx), static_cast<unsigned>(ceil_div(tiles, per))), 256,
-           static_cast<size_t>(per) * 1024 * L.kt, s>>>(rf, L.kt, L.d, L.k, Tp,
-                                                        static_cast<int>(splits), W, m, ldw,
-                                                        static_cast<int>(per));
+        <<<grid, 256, static_cast<size_t>(per) * 1024 * L.kt, s>>>(
+            rf, L.kt, L.d, L.k, Tp, static_cast<int>(splits), W, m, ldw, static_cast<int>(per));
     return hipGetLastError();
   };
   const std::integral_constant<int, 2> two{};

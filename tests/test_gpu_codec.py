@@ -419,6 +419,24 @@ def test_generic_weights_edges(dtype, d, k, m, pad):
         assert np.all(np.abs(host(W).T - ref) <= tol)
 
 
+def test_generic_weights_of_a_million_rows():
+    """More row ranges than one grid dimension takes (d = 1100003, k = 250: 34376
+    ranges of two 16-row tiles), every element against float64."""
+    log("[generic weights] d=1100003 k=250 m=3")
+    d, k, m = 1100003, 250, 3
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    U = torch.randn(d, k, generator=g, device="cuda") * d ** -0.5
+    W = torch.randn(d, m, generator=g, device="cuda")
+    t, step = torch.zeros(k, m, device="cuda", dtype=torch.float64), 1 << 18
+    for r in range(0, d, step):
+        t += U[r:r + step].double().T.contiguous() @ W[r:r + step].double()
+    ref = torch.cat([U[r:r + step].double() @ t for r in range(0, d, step)])
+    sn.sn_project_weights(sn.sn_basis_pack(U), W)
+    # one rounding (2^-24 of the value) of float64 sums of k terms of about |t| |u|
+    assert bool(((W.double() - ref).abs() <= 2.0 ** -22 * ref.abs() + 1e-12).all())
+
+
 @pytest.mark.parametrize("dtype,d,k,n", [("f32", 7, 3, 1), ("f32", 33, 17, 65), ("f32", 130, 70, 31),
                                          ("f32", 300, 128, 1000), ("bf16", 100, 20, 129)])
 def test_generic_subspace_edges(dtype, d, k, n):
