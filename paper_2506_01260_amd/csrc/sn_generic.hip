@@ -660,10 +660,9 @@ __global__ __launch_bounds__(256) void decompress_f64_kernel(
   }
   __syncthreads();
   for (int r = r0; r < r1; r += 2) {
-    if constexpr (TAB) {  // past the range the last pair's again, unused
-      const int rn = r + 2 < r1 ? r + 2 : r;
-      load_tab(nxt[0], rn);
-      load_tab(nxt[1], rn + 1);
+    if (TAB && r + 2 < r1) {  // a range of one pair (few tokens) waits for no more loads
+      load_tab(nxt[0], r + 2);
+      load_tab(nxt[1], r + 3);
     }
     f64x4 a0 = start(cur[0], r), a1 = start(cur[1], r + 1);
     const f32x4 *f0 = us + (r - r0) * kt * 64 + lane;
