@@ -993,7 +993,9 @@ def test_id_check_mode_raises_index_error():
 def test_native_calls_and_python_form_agree(monkeypatch):
     """Each call through the native marshalling and through the Python form of
     the same function: bit-equal results, and what the native form leaves to
-    Python (a wrong dtype, shape, stride, an odd object) raises there."""
+    Python (a wrong dtype, shape, stride, an odd object) raises there.  The
+    native form takes every one of these calls itself, and leaves the operands of
+    those it does not take as they were."""
     d, k, n = 256, 24, 70
     st, o, tok, pos = _small(d, k, n, dtype="bf16", seed=3)
     basis = sn.sn_basis_pack(dev(st["U"], "bf16"))
@@ -1026,7 +1028,22 @@ def test_native_calls_and_python_form_agree(monkeypatch):
         torch.cuda.synchronize()
         return [g.clone() for g in got]
 
+    calls, taken = sn._native(), {}
+
+    class Recorder:
+        def __getattr__(self, name):
+            def call(*args):
+                out = getattr(calls, name)(*args)
+                taken.setdefault(name, []).append(out is not None)
+                return out
+            return call
+
+    monkeypatch.setattr(sn, "_native", Recorder)
     native = every()
+    assert set(taken) == {"compress", "decompress", "grad_compress", "compress_projected",
+                          "project_weights", "project_weights_multi", "grassmann_accumulate",
+                          "embed_lowrank_forward", "embed_lowrank_backward", "adamw_step"}
+    assert all(all(t) for t in taken.values()), taken  # no ordinary call was left to Python
     monkeypatch.setattr(sn, "_native", lambda: None)
     python = every()
     for i, (a, b) in enumerate(zip(native, python)):
@@ -1034,13 +1051,34 @@ def test_native_calls_and_python_form_agree(monkeypatch):
         assert torch.equal(a.contiguous().view(torch.uint8), b.contiguous().view(torch.uint8)), i
     monkeypatch.undo()
 
-    calls = sn._native()
+    # what the native form leaves to Python it leaves untouched
+    W, A, M, V = W0.clone(), W0.clone(), M0.clone(), V0.clone()
+    gcs, state = torch.zeros(E.shape[0], k, device="cuda"), sn.sn_grassmann_state(basis)
+    out, wide = torch.zeros(n, k, device="cuda", dtype=torch.bfloat16), torch.zeros_like(X)
+    small = torch.empty(1, dtype=torch.uint8, device="cuda")
+    held = [W, A, M, V, gcs, state.buf, out, wide]
+    before = [h.clone() for h in held]
+    for left in (calls.compress(basis, X.float(), t, E, P, None, 9, out, None, None),
+                 calls.decompress(basis, C, t[:-1], E, P, None, 9, wide, None, None),
+                 calls.compress_projected(basis, X, proj, t.long(), None, 9, out, None, None),
+                 calls.project_weights(basis, W, small, None),
+                 calls.project_weights_multi(basis, [W, W.float()], None, None),
+                 calls.grassmann_accumulate(basis, G, state, True, True, out, small, None),
+                 calls.embed_lowrank_forward(basis, CS, t, E[:-1], P, None, 9, wide, None, None, None),
+                 calls.embed_lowrank_backward(basis, G, t, gcs, None, small, None),
+                 calls.adamw_step(A, W0, M, V[:, :8], 3, 1e-3, 0.9, 0.999, 1e-8, 0.1, True, None,
+                                  None)):
+        assert left is None
+    for i, (h, b) in enumerate(zip(held, before)):
+        assert torch.equal(h.view(torch.uint8), b.view(torch.uint8)), i
+    assert calls.grad_compress(basis, G[:1].expand(n, d), None, None) is None  # overlapping rows
     assert calls.grad_compress(basis, G.float(), None, None) is None
     assert calls.grad_compress(basis, G.t(), None, None) is None
     assert calls.grad_compress(basis, [1], None, None) is None
     assert calls.grad_compress(object(), G, None, None) is None
     for bad, status in ((lambda: sn.sn_grad_compress(basis, G.float()), 3),
                         (lambda: sn.sn_grad_compress(basis, G[:, :-1]), 2),
+                        (lambda: sn.sn_grad_compress(basis, G[:1].expand(n, d)), 2),
                         (lambda: sn.sn_compress(basis, X, tok=t[:-1], E=E), 2),
                         (lambda: sn.sn_compress(basis, X, P=P, seq_len=0), 2),
                         (lambda: sn.sn_grad_compress(basis, G, out=G[:, :k]), 5)):
