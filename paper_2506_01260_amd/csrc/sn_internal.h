@@ -204,11 +204,12 @@ hipError_t launch_grass_compress_split(const PackLayout &L, const void *packed, 
 int64_t grass_compress_groups(const PackLayout &L, int64_t N, int64_t *steps);
 // Tp[split][i][j] = sum over the split's token rows n of F[n, j] G[n, i]
 // (F in the kfrag layout with ktb column tiles and npad rows, zero past N).
-// Columns of G per lane in that kernel, for ktb column tiles of the operand.
-int grass_tokens_cols(int ktb);
 hipError_t launch_grass_tokens_mfma(const void *frag, int ktb, int64_t npad, const void *G,
                                     int64_t N, int64_t ldg, int64_t d, int64_t rows, int ds,
                                     int64_t m_pad, float *Tp, hipStream_t s);
+// Columns of G per lane in that kernel: 16-byte row pieces up to 5 column tiles of
+// the operand (the accumulators then live in the AGPRs), else 8-byte ones.
+constexpr int grass_tokens_cols(int ktb) { return ktb <= 5 ? 8 : 4; }
 
 // Generic path (any shape and dtype, k <= kGrassMaxK), all float64: C64 = G U
 // (N x k); the loss sum (g - c U^T)^2 per workgroup into part; the token

@@ -445,15 +445,10 @@ int64_t pass1_slots(int kt) {
 // split's rows n of F[n, j] G[n, i], F the (npad x 16 ktb) operand in the kfrag
 // layout (zero past N), G the N x d gradient; the pass-1 kernel with the
 // roles d -> tokens, W -> G, U -> F.
-// 16-byte row pieces (8 columns per lane) up to 5 column tiles: the
-// accumulators then live in the AGPRs
-template <int KT>
-constexpr int tok_cw() { return KT <= 5 ? 8 : 4; }
-
 template <int KT>
 void launch_p1_tokens(const bf16_t *frag, int64_t npad, const bf16_t *G, int64_t N, int64_t ldg,
                       int64_t d, int64_t rows, int ds, int64_t m_pad, float *Tp, hipStream_t s) {
-  constexpr int CW = tok_cw<KT>();
+  constexpr int CW = grass_tokens_cols(KT);
   const unsigned blocks = static_cast<unsigned>(ceil_div(d, 16 * CW));
   // Eight splits along x go to the eight XCDs; with the column blocks along x
   // every XCD reads the whole operand.  d = 4096, k = 40 (32 blocks), 32768
@@ -465,8 +460,6 @@ void launch_p1_tokens(const bf16_t *frag, int64_t npad, const bf16_t *G, int64_t
   project_pass1_kernel<KT, true, CW><<<grid, kBlock, 0, s>>>(frag, npad, one_seg(G, d, ldg),
                                                               rows, m_pad, Tp, N, split_x);
 }
-
-int grass_tokens_cols(int ktb) { return ktb <= 5 ? tok_cw<1>() : tok_cw<kMfmaMaxKT>(); }
 
 hipError_t launch_grass_tokens_mfma(const void *frag, int ktb, int64_t npad, const void *G,
                                     int64_t N, int64_t ldg, int64_t d, int64_t rows, int ds,
