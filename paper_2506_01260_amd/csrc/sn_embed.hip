@@ -35,7 +35,8 @@ EmbedPlan embed_plan(int64_t k, int dt, int64_t N, int64_t vocab, bool backward)
   P.kp = 16 * ceil_div(k, 16);
   size_t off = 0;
   P.off_c = off;
-  // forward: the gathered coefficients (N x k, dt); backward: fp32 rows of kp
+  // forward: the gathered coefficients (N x k, dt; left alone where the decompress
+  // reads C_S by id, which the sizes alone don't tell); backward: fp32 rows of kp
   const size_t cbytes = backward ? static_cast<size_t>(N) * P.kp * 4
                                  : static_cast<size_t>(N) * k * (dt == 0 ? 4 : 2);
   off = align256(off + cbytes);
