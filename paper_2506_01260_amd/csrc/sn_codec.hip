@@ -255,6 +255,14 @@ __device__ __forceinline__ void wait_vm_upto(int v) {
 // output is given (see GrassOut).
 enum Epi { kEpiBf16 = 0, kEpiProjected = 1, kEpiF32 = 2, kEpiGrass = 3 };
 
+// Columns j .. j + 3 of a projected table's row: zero past column k, also where
+// the row's infinities times U's zero padding are not.
+__device__ __forceinline__ f32x4 table_cols(f32x4 v, int64_t j, int64_t k) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = j + e < k ? v[e] : 0.0f;
+  return v;
+}
+
 template <int KT, bool HE, bool HP, int BP, int NW, int EPI>
 __global__ __launch_bounds__(threads_c<NW>()) void compress_kernel(const bf16_t *__restrict__ kfrag,
                                                              int64_t d, int64_t k,
@@ -657,8 +665,8 @@ __global__ __launch_bounds__(threads_c<NW>()) void compress_kernel(const bf16_t 
   for (int t = 0; t < KT; ++t) {
     const f32x4 v = acc[t];
     const int64_t j = 16 * t + 4 * g;
-    if (EPI == kEpiF32) {  // full padded row of the projected table (columns >= k are 0)
-      *reinterpret_cast<f32x4 *>(static_cast<float *>(Cout) + tok * ldc + j) = v;
+    if (EPI == kEpiF32) {  // full padded row of the projected table
+      *reinterpret_cast<f32x4 *>(static_cast<float *>(Cout) + tok * ldc + j) = table_cols(v, j, k);
       continue;
     }
     bf16_t *dst = static_cast<bf16_t *>(Cout) + tok * ldc + j;
@@ -786,8 +794,8 @@ __global__ __launch_bounds__(kThreads) void stream_compress_kernel(
   for (int t = 0; t < KT; ++t) {
     const f32x4 v = acc[t];
     const int64_t j = 16 * t + 4 * g;
-    if (EPI == kEpiF32) {  // full padded row of the projected table (columns >= k are 0)
-      *reinterpret_cast<f32x4 *>(static_cast<float *>(Cout) + it * ldc + j) = v;
+    if (EPI == kEpiF32) {  // full padded row of the projected table
+      *reinterpret_cast<f32x4 *>(static_cast<float *>(Cout) + it * ldc + j) = table_cols(v, j, k);
       continue;
     }
     bf16_t *dst = static_cast<bf16_t *>(Cout) + it * ldc + j;

@@ -451,7 +451,7 @@ __global__ __launch_bounds__(64 * NW) void compress_f64_kernel(
 #pragma unroll
       for (int w = 1; w < NW; ++w) v += red[w][t][16 * gg + nn][q];
       if (mode == kGenTable) {
-        static_cast<float *>(out)[tok * ldc + j] = static_cast<float>(v);
+        static_cast<float *>(out)[tok * ldc + j] = j < k ? static_cast<float>(v) : 0.0f;
       } else if (mode == kGenF64) {
         static_cast<double *>(out)[tok * ldc + j] = v;
       } else {

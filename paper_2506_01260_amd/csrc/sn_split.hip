@@ -263,8 +263,8 @@ __global__ __launch_bounds__(kSThreads) void compress_split_kernel(
     const int row = e / (16 * KT), j = e % (16 * KT);
     const int64_t tok = i0 + row;
     if (tok >= N) break;  // rows ascend with e
-    if (OUT == kOutF32) {  // the full padded row (columns >= k are 0)
-      static_cast<float *>(Cout)[tok * ldc + j] = total(row, j);
+    if (OUT == kOutF32) {  // the full padded row, zero past column k
+      static_cast<float *>(Cout)[tok * ldc + j] = j < k ? total(row, j) : 0.0f;
       continue;
     }
     if (j >= k) continue;

@@ -139,3 +139,23 @@ def test_projected_configs(cfg_id):
                        dt, f"cfg{cfg_id} compress_projected (every row)")
     torch.cuda.synchronize()
     assert int(flag.item()) == 0
+
+
+@pytest.mark.parametrize("dtype,d,rows,pad", [("f32", 100, 70, 0), ("bf16", 256, 70, 1),
+                                              ("bf16", 256, 70, 0), ("bf16", 256, 5000, 0),
+                                              ("bf16", 96, 8200, 0)])
+def test_table_padding_is_zero_beside_infinities(dtype, d, rows, pad):
+    """Columns k .. kp - 1 of a projected table are zero, also in rows whose
+    infinities and NaN meet U's zero padding, in each kernel that builds tables
+    (float64, few-token, staged, streaming)."""
+    log(f"[projected] zero padding {dtype} d={d} rows={rows} pad={pad}")
+    k, t = 20, torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d + rows)
+    U = torch.randn(d, k, generator=g, device="cuda").to(t)
+    E = torch.randn(rows, d + pad, generator=g, device="cuda").to(t)[:, :d]
+    E[3, 5], E[4, 0], E[rows - 1, d - 1] = float("inf"), float("nan"), -float("inf")
+    eu, _ = sn.sn_embed_project(sn.sn_basis_pack(U), E=E).tables()
+    assert eu.shape == (rows, 32) and bool((eu[:, k:] == 0).all())
+    finite = torch.isfinite(E.float()).all(1)
+    assert bool(torch.isfinite(eu[finite]).all()) and not bool(torch.isfinite(eu[~finite, :k]).any())
