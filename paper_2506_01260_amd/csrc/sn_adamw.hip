@@ -196,7 +196,7 @@ __global__ __launch_bounds__(64 * kAlphaWaves) void alpha_kernel(
     double eps, float *__restrict__ alpha) {
   __shared__ double red[kAlphaWaves][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t c = static_cast<int64_t>(blockIdx.x) * 64 + lane;
+  const int64_t c = (static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x) * 64 + lane;
   double s = 0.0;
   if (c < cols) {
 #pragma unroll 8
@@ -268,7 +268,10 @@ hipError_t launch_t(void *Wv, int64_t ldw, const void *Gv, int64_t ldg, float *M
   float *alpha = colsum + static_cast<int64_t>(grid.y) * cols;
   moments_kernel<T, VEC, true, kSubCT, kSubRG, kSubR><<<grid, kSubCT * kSubRG, 0, s>>>(
       W, ldw, G, ldg, M, V, ldm, rows, cols, a, colsum);
-  alpha_kernel<<<dim3(static_cast<unsigned>(ceil_div(cols, 64))), 64 * kAlphaWaves, 0, s>>>(
+  // a grid dimension holds fewer than 2^32 threads, 2^23 of these workgroups
+  const int64_t groups = ceil_div(cols, 64), gx = groups < (1 << 22) ? groups : 1 << 22;
+  const dim3 ga(static_cast<unsigned>(gx), static_cast<unsigned>(ceil_div(groups, gx)));
+  alpha_kernel<<<ga, 64 * kAlphaWaves, 0, s>>>(
       colsum, grid.y, rows, cols, inv_bc2, eps, alpha);
   apply_kernel<T, VEC, kSubCT, kSubRG, kSubR><<<grid, kSubCT * kSubRG, 0, s>>>(
       W, ldw, G, ldg, M, ldm, rows, cols, a, alpha);

@@ -69,7 +69,7 @@ __global__ __launch_bounds__(256) void pack_frag32_kernel(const T *__restrict__ 
                                                           int64_t k, int64_t ldu, int kt,
                                                           f32x4 *__restrict__ kfrag,
                                                           f32x4 *__restrict__ rfrag) {
-  int64_t slot = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  int64_t slot = (static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
   const int64_t nk = (d + 31) / 32 * kt * 128, nr = (d + 15) / 16 * kt * 64;
   const bool second = slot >= nk;
   if (second) slot -= nk;
@@ -188,7 +188,10 @@ hipError_t launch_pack(const PackLayout &L, const void *U, int64_t ldu, void *pa
                                                  reinterpret_cast<float *>(base + L.off_f32));
   {
     const int64_t slots = ceil_div(L.d, 32) * L.kt * 128 + ceil_div(L.d, 16) * L.kt * 64;
-    const dim3 gf(static_cast<unsigned>(ceil_div(slots, 256)));
+    // 8 threads per row and column tile: more than one grid dimension's 2^32 above
+    // 2^29 rows
+    const int64_t blocks = ceil_div(slots, 256), gx = blocks < (1 << 23) ? blocks : 1 << 23;
+    const dim3 gf(static_cast<unsigned>(gx), static_cast<unsigned>(ceil_div(blocks, gx)));
     f32x4 *kf = reinterpret_cast<f32x4 *>(base + L.off_kfrag32);
     f32x4 *rf = reinterpret_cast<f32x4 *>(base + L.off_rfrag32);
     if (L.dt == 0)

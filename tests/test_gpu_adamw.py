@@ -110,3 +110,24 @@ def test_adamw_deterministic():
     b, _ = _case("bf16", 512, 1000, 2, 2, True)
     for x, y in zip(a, b):
         assert np.array_equal(x, y)
+
+
+def test_subspace_step_of_more_than_2_29_columns():
+    """One row of 2^29 + 77 columns: the column rates' workgroups take more than
+    one grid dimension's threads.  With one row each rate is the entrywise one."""
+    log("[adamw] 1 x 2^29 + 77, bf16")
+    n = (1 << 29) + 77
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    W = torch.randn(1, n, generator=g, device="cuda", dtype=torch.bfloat16)
+    G = torch.randn(1, n, generator=g, device="cuda", dtype=torch.bfloat16)
+    M, V = torch.zeros(1, n, device="cuda"), torch.zeros(1, n, device="cuda")
+    W0 = W.clone()
+    sn.sn_adamw_step(W, G, M, V, 1, 0.25, weight_decay=0.0)
+    for a in list(range(0, n, 1 << 26)) + [n - 4096]:
+        b = slice(a, min(n, a + (1 << 14)))
+        gd = G[0, b].double()  # t = 1: M^ / (sqrt(V^) + eps) = G / (|G| + eps)
+        ref = W0[0, b].double() - 0.25 * gd / (gd.abs() + 1e-8)
+        # one bf16 rounding, and float32 roundings of a step of 0.25
+        err = (W[0, b].double() - ref).abs() - 2.0 ** -8 * ref.abs()
+        assert float(err.max()) <= 1e-6, (a, float(err.max()))

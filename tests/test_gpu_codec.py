@@ -419,6 +419,20 @@ def test_generic_weights_edges(dtype, d, k, m, pad):
         assert np.all(np.abs(host(W).T - ref) <= tol)
 
 
+def test_basis_of_more_than_2_29_rows():
+    """A basis of 2^29 + 33 rows, whose operand sections take more threads to pack
+    than one grid dimension has: its last rows arrive in both."""
+    log("[pack] d=2^29+33 k=1, float32")
+    d = (1 << 29) + 33
+    U = torch.zeros(d, 1, device="cuda")
+    U[d - 1], U[d - 40], U[7] = 2.0, 3.0, 4.0
+    basis = sn.sn_basis_pack(U)
+    C = sn.sn_grad_compress(basis, torch.ones(1, d, device="cuda"))
+    assert float(C) == 9.0
+    X = sn.sn_decompress(basis, torch.ones(1, 1, device="cuda"))
+    assert torch.equal(X[0], U[:, 0])
+
+
 def test_generic_weights_of_a_million_rows():
     """More row ranges than one grid dimension takes (d = 1100003, k = 250: 34376
     ranges of two 16-row tiles), every element against float64."""
