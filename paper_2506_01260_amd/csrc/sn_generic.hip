@@ -16,6 +16,15 @@
 
 namespace sn {
 
+// A grid dimension holds fewer than 2^32 threads, and a grid past that is cut off
+// without an error: workgroup counts that follow the tokens or columns are laid
+// over x and another dimension.
+constexpr int64_t kGridX = int64_t{1} << 21;
+inline int64_t grid_x(int64_t groups) { return groups < kGridX ? groups : kGridX; }
+inline unsigned grid_more(int64_t groups) {
+  return static_cast<unsigned>(ceil_div(groups, grid_x(groups)));
+}
+
 // ---------------------------------------------------------------------------
 // Packing
 // ---------------------------------------------------------------------------
@@ -190,8 +199,8 @@ hipError_t launch_pack(const PackLayout &L, const void *U, int64_t ldu, void *pa
     const int64_t slots = ceil_div(L.d, 32) * L.kt * 128 + ceil_div(L.d, 16) * L.kt * 64;
     // 8 threads per row and column tile: more than one grid dimension's 2^32 above
     // 2^29 rows
-    const int64_t blocks = ceil_div(slots, 256), gx = blocks < (1 << 23) ? blocks : 1 << 23;
-    const dim3 gf(static_cast<unsigned>(gx), static_cast<unsigned>(ceil_div(blocks, gx)));
+    const int64_t blocks = ceil_div(slots, 256);
+    const dim3 gf(static_cast<unsigned>(grid_x(blocks)), grid_more(blocks));
     f32x4 *kf = reinterpret_cast<f32x4 *>(base + L.off_kfrag32);
     f32x4 *rf = reinterpret_cast<f32x4 *>(base + L.off_rfrag32);
     if (L.dt == 0)
@@ -341,7 +350,8 @@ __global__ __launch_bounds__(64 * NW) void compress_f64_kernel(
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, n = lane & 15;
-  const int64_t i0 = 16 * static_cast<int64_t>(blockIdx.x);
+  const int64_t i0 = 16 * (static_cast<int64_t>(blockIdx.z) * gridDim.x + blockIdx.x);
+  if (i0 >= N) return;
   const int64_t i = i0 + n < N ? i0 + n : N - 1;  // rows past N repeat the last, not stored
   const int t0 = static_cast<int>(blockIdx.y) * KT;  // first column tile
   const T *xr = X + i * ldx;
@@ -485,15 +495,16 @@ void launch_compress_f64(const PackLayout &L, const void *packed, const void *X,
                          int64_t ldc, hipStream_t s) {
   const f32x4 *kf =
       reinterpret_cast<const f32x4 *>(static_cast<const char *>(packed) + L.off_kfrag32);
-  const dim3 grid(static_cast<unsigned>(ceil_div(N, 16)),
-                  static_cast<unsigned>(ceil_div(L.kt, KT)));
+  const int64_t tiles = ceil_div(N, 16);
+  const dim3 grid(static_cast<unsigned>(grid_x(tiles)),
+                  static_cast<unsigned>(ceil_div(L.kt, KT)), grid_more(tiles));
   const T *x = static_cast<const T *>(X);
   auto go = [&](auto nw) {
     constexpr int NW = decltype(nw)::value;
     compress_f64_kernel<T, KT, NW, TAB>
         <<<grid, 64 * NW, 0, s>>>(kf, L.kt, L.d, L.k, x, N, ldx, ids, pa, mode, out, ldc);
   };
-  const int64_t groups = static_cast<int64_t>(grid.x) * grid.y;
+  const int64_t groups = tiles * grid.y;
   if (KT <= 4 && groups <= 512)
     go(std::integral_constant<int, KT <= 4 ? 16 : 8>{});
   else if (groups <= 1024)
@@ -775,10 +786,13 @@ __global__ __launch_bounds__(256) void project_t_f64_kernel(const f32x4 *__restr
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, n = lane & 15;
-  const int64_t cb = 64 * static_cast<int64_t>(blockIdx.x);
+  // z: the column tiles of U, and over them the column blocks that x leaves
+  const int nz = (kt + KT - 1) / KT;
+  const int64_t cb = 64 * (static_cast<int64_t>(blockIdx.z / nz) * gridDim.x + blockIdx.x);
+  if (cb >= m) return;
   const int64_t c0 = cb + 4 * n;
   const bool whole = c0 + 4 <= m;
-  const int t0 = static_cast<int>(blockIdx.z) * KT;
+  const int t0 = static_cast<int>(blockIdx.z % nz) * KT;
   const int units = static_cast<int>((d + 31) / 32);
   const int u0 = static_cast<int>(blockIdx.y) * units_per_split;
   const int u1 = u0 + units_per_split < units ? u0 + units_per_split : units;
@@ -886,8 +900,12 @@ __global__ __launch_bounds__(256) void project_w_f64_kernel(const f32x4 *__restr
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, n = lane & 15;
   const int ntile = static_cast<int>((d + 15) / 16);
-  const int64_t range = static_cast<int64_t>(blockIdx.z) * gridDim.y + blockIdx.y;
-  if (range * tiles_per_wg >= ntile) return;
+  // z: the ranges that y leaves, and over them the column blocks that x leaves
+  const int64_t ranges = (ntile + tiles_per_wg - 1) / tiles_per_wg;
+  const unsigned nz = static_cast<unsigned>((ranges + gridDim.y - 1) / gridDim.y);
+  const int64_t range = static_cast<int64_t>(blockIdx.z % nz) * gridDim.y + blockIdx.y;
+  const int64_t cblk = static_cast<int64_t>(blockIdx.z / nz) * gridDim.x + blockIdx.x;
+  if (range >= ranges) return;
   const int r0 = static_cast<int>(range) * tiles_per_wg;
   const int r1 = r0 + tiles_per_wg < ntile ? r0 + tiles_per_wg : ntile;
   for (int e = threadIdx.x; e < (r1 - r0) * kt * 64; e += 256)
@@ -897,7 +915,7 @@ __global__ __launch_bounds__(256) void project_w_f64_kernel(const f32x4 *__restr
   double tb[NT][4 * KG];  // T[4 s + g][col] of step s
 #pragma unroll
   for (int b = 0; b < NT; ++b) {
-    col[b] = (static_cast<int64_t>(blockIdx.x) * 4 + wave) * (16 * NT) + 16 * b + n;
+    col[b] = (cblk * 4 + wave) * (16 * NT) + 16 * b + n;
     const int64_t c = col[b] < m ? col[b] : m - 1;
 #pragma unroll
     for (int st = 0; st < 4 * KG; ++st) tb[b][st] = 0.0;
@@ -955,8 +973,8 @@ hipError_t project_f64(const PackLayout &L, const void *packed, T *W, int64_t m,
   splits = splits < ceil_div(units, 4) ? splits : ceil_div(units, 4);
   const int64_t ups = ceil_div(units, splits);
   splits = ceil_div(units, ups);
-  const dim3 g1(static_cast<unsigned>(cblocks), static_cast<unsigned>(splits),
-                static_cast<unsigned>(z));
+  const dim3 g1(static_cast<unsigned>(grid_x(cblocks)), static_cast<unsigned>(splits),
+                static_cast<unsigned>(z) * grid_more(cblocks));
   auto pass1 = [&](auto kt) {
     project_t_f64_kernel<T, decltype(kt)::value, false><<<g1, 256, 0, s>>>(
         kf, nullptr, L.kt, L.d, L.k, W, m, ldw, static_cast<int>(ups), Tp);
@@ -975,8 +993,8 @@ hipError_t project_f64(const PackLayout &L, const void *packed, T *W, int64_t m,
     int64_t per = ceil_div(tiles, ceil_div(512, gx));
     per = per < 32 / L.kt ? per : 32 / L.kt;
     const int64_t ranges = ceil_div(tiles, per), gy = ranges < 32768 ? ranges : 32768;
-    const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(gy),
-                    static_cast<unsigned>(ceil_div(ranges, gy)));
+    const dim3 grid(static_cast<unsigned>(grid_x(gx)), static_cast<unsigned>(gy),
+                    static_cast<unsigned>(ceil_div(ranges, gy)) * grid_more(gx));
     project_w_f64_kernel<T, KG, NT>
         <<<grid, 256, static_cast<size_t>(per) * 1024 * L.kt, s>>>(
             rf, L.kt, L.d, L.k, Tp, static_cast<int>(splits), W, m, ldw, static_cast<int>(per));
@@ -1038,9 +1056,12 @@ __global__ __launch_bounds__(256) void gen_loss_kernel(const f32x4 *__restrict__
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, n = lane & 15;
-  const int64_t tg = blockIdx.x % tgroups;
+  const int64_t wg = static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x;
+  const int64_t tg = wg % tgroups;
   const int ntile = static_cast<int>((d + 15) / 16);
-  const int r0 = 2 * static_cast<int>(blockIdx.x / tgroups) * pairs_per_wg;
+  const int64_t first = 2 * (wg / tgroups) * pairs_per_wg;
+  if (first >= ntile) return;  // past the last workgroup
+  const int r0 = static_cast<int>(first);
   const int r1 = r0 + 2 * pairs_per_wg < ntile ? r0 + 2 * pairs_per_wg : ntile;
   const int64_t i = 16 * (tg * 4 + wave) + n;
   const bool live = i < N;
@@ -1084,7 +1105,7 @@ __global__ __launch_bounds__(256) void gen_loss_kernel(const f32x4 *__restrict__
     if (static_cast<int>(threadIdx.x) < w) red[threadIdx.x] += red[threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+  if (threadIdx.x == 0) part[wg] = red[0];
 }
 
 template <typename T>
@@ -1095,7 +1116,8 @@ hipError_t gen_loss(const PackLayout &L, const void *packed, const T *G, int64_t
   const GenLossGrid gg = gen_loss_grid(N, L.d);
   auto go = [&](auto kg) {
     gen_loss_kernel<T, decltype(kg)::value>
-        <<<dim3(static_cast<unsigned>(gg.tgroups * gg.cols)), 256, 0, s>>>(
+        <<<dim3(static_cast<unsigned>(grid_x(gg.tgroups * gg.cols)),
+                grid_more(gg.tgroups * gg.cols)), 256, 0, s>>>(
             rf, L.kt, L.d, L.k, C64, G, N, ldg, gg.tgroups, static_cast<int>(gg.per), part);
     return hipGetLastError();
   };
@@ -1133,8 +1155,9 @@ hipError_t gen_tokens(const PackLayout &L, const T *G, int64_t N, int64_t ldg, c
                       double *Tp, hipStream_t s) {
   const int64_t units = ceil_div(N, 32), splits = gen_token_splits(N, L.d, L.k);
   const int kt1 = L.kt < 4 ? L.kt : 4;
-  const dim3 grid(static_cast<unsigned>(ceil_div(L.d, 64)), static_cast<unsigned>(splits),
-                  static_cast<unsigned>(ceil_div(L.kt, kt1)));
+  const int64_t cblocks = ceil_div(L.d, 64);
+  const dim3 grid(static_cast<unsigned>(grid_x(cblocks)), static_cast<unsigned>(splits),
+                  static_cast<unsigned>(ceil_div(L.kt, kt1)) * grid_more(cblocks));
   const int ups = static_cast<int>(ceil_div(units, splits));
   auto go = [&](auto kt) {
     project_t_f64_kernel<T, decltype(kt)::value, true>

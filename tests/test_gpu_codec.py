@@ -433,6 +433,30 @@ def test_basis_of_more_than_2_29_rows():
     assert torch.equal(X[0], U[:, 0])
 
 
+def test_generic_kernels_past_2_32_threads():
+    """Token and column counts whose workgroups take more threads than one grid
+    dimension has (float32, d = k = 1, U = 1/2: every result is exact): compress
+    and accumulate of 2^30 + 65 tokens, projection of 2^30 + 129 columns."""
+    log("[generic] d=k=1, 2^30 + 65 tokens, 2^30 + 129 columns")
+    n, m = (1 << 30) + 65, (1 << 30) + 129
+    basis = sn.sn_basis_pack(torch.full((1, 1), 0.5, device="cuda"))
+    G = torch.ones(n, 1, device="cuda")
+    G[n - 70:, 0] = 2.0
+    state = sn.sn_grassmann_state(basis)
+    Cg = sn.sn_grassmann_accumulate(basis, G, state, want_cg=True)
+    energy = float(n - 70 + 4 * 70)
+    assert float(state.scalars()[0]) == 0.5625 * energy and float(state.Y()) == 0.5 * energy
+    assert bool((Cg == 0.5 * G).all())
+    del Cg
+    C = sn.sn_compress(basis, G)
+    assert bool((C == 0.5 * G).all())
+    del C, G
+    W = torch.ones(1, m, device="cuda")
+    W[0, m - 200:] = 4.0
+    sn.sn_project_weights(basis, W)
+    assert bool((W[0, :m - 200] == 0.25).all()) and bool((W[0, m - 200:] == 1.0).all())
+
+
 def test_generic_weights_of_a_million_rows():
     """More row ranges than one grid dimension takes (d = 1100003, k = 250: 34376
     ranges of two 16-row tiles), every element against float64."""
