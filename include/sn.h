@@ -81,7 +81,9 @@ typedef void *sn_stream;
 /* (Sec. 4.5: a Grassmann step every few hundred iterations), so it is packed */
 /* once into the layouts the kernels read, and every codec call takes the     */
 /* packed buffer.  Re-pack after any change to U; a stale pack is not         */
-/* detected.                                                                  */
+/* detected.  The layout is the library build's own: keep U, not the packed   */
+/* buffer, across builds (a newer layout may be larger and is then read past  */
+/* the buffer's end).                                                         */
 /* ------------------------------------------------------------------------ */
 
 /* Size in bytes of the packed form of a d x k basis of element type dt

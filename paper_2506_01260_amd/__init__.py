@@ -218,7 +218,16 @@ class Basis:
     """A packed basis (the device buffer the codec calls read) plus its shape."""
 
     def __init__(self, packed: torch.Tensor, d: int, k: int, dt: int):
-        self.packed, self.d, self.k, self.dt = packed, d, k, dt
+        self.__setstate__({"packed": packed, "d": d, "k": k, "dt": dt})
+
+    def __setstate__(self, state):
+        # a buffer kept from a build with a smaller layout would be read past its end
+        need = sn_basis_packed_bytes(state["d"], state["k"], state["dt"])
+        have = state["packed"].numel() * state["packed"].element_size()
+        if need == 0 or have < need:
+            raise SnError(9, f"packed basis of {have} bytes, this library's layout takes {need}: "
+                             "pack U again")
+        self.__dict__.update(state)
 
     @property
     def ptr(self):

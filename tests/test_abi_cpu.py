@@ -154,6 +154,25 @@ def test_binding_rejects_overlapping_rows():
     assert sn._mat(_Device(torch.zeros(5, 1)[:, :1]), "X")[1:] == (5, 1, 1)
 
 
+def test_basis_of_another_layout_is_refused():
+    """A packed buffer smaller than this library's layout (one kept from another
+    build) is refused when it becomes a basis, directly or from a pickle."""
+    import pickle
+
+    import torch
+    d, k, dt = 256, 8, sn.SN_BF16
+    need = sn.sn_basis_packed_bytes(d, k, dt)
+    whole = sn.Basis(torch.zeros(need, dtype=torch.uint8), d, k, dt)
+    again = pickle.loads(pickle.dumps(whole))
+    assert (again.d, again.k, again.dt, again.packed.numel()) == (d, k, dt, need)
+    whole.packed = whole.packed[:need - 256].clone()
+    for make in (lambda: sn.Basis(whole.packed, d, k, dt),
+                 lambda: pickle.loads(pickle.dumps(whole))):
+        with pytest.raises(sn.SnError) as e:
+            make()
+        assert e.value.status == 9
+
+
 def test_binding_rejects_host_tensors():
     import torch
     U = torch.zeros(64, 8, dtype=torch.bfloat16)
