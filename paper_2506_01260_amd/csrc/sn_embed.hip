@@ -108,8 +108,9 @@ __device__ __forceinline__ int clamp_tok(const int32_t *tok, int64_t i, int64_t 
 // ascending order.  rid[b][r] = the id of run r (ascending); first[q][b] =
 // the first run with an id of at least q kIdRange (q = 0 .. nq, first[nq][b]
 // = the runs; blocks along the row, so id_merge_kernel's lanes read one
-// line: 10.0 -> 9.7 us at 16384 tokens, vocabulary 32000); part[b][r][:] = the float64 sum of the run's c32 rows in
-// order.  Wave w sums the sorted positions 64 w .. 64 w + 63 (lane = column,
+// line: 10.0 -> 9.7 us at 16384 tokens, vocabulary 32000);
+// part[b][r][:] = the float64 sum of the run's c32 rows in order.
+// Wave w sums the sorted positions 64 w .. 64 w + 63 (lane = column,
 // 64 columns per pass): a run that begins and ends inside the wave is written
 // directly; a run that crosses waves leaves its first and middle pieces in
 // LDS and the wave where it ends adds them in order.  Ids must be below 2^21.

@@ -13,7 +13,8 @@
 // reading U once per 16 tokens instead of once per 64 or 128.  Bound by the
 // bytes a CU takes in (786 KB of rows and U at d = 4096, k = 40) and by the
 // latency of the ids, rows and sums before and after.  d = 4096, k = 40, both
-// tables: 1024 tokens 37 -> 12.7 us, 4096 tokens 36.6 -> 15.1 us.
+// tables: 1024 tokens 35.4 -> 12.8 us, 4096 tokens 36.6 -> 21.3 us (16.6 where the
+// activation and its embedding rows are cached from the call before).
 //
 // The rows go through LDS although each wave reads only its own: the MFMA
 // operand layout gives consecutive lanes different rows, and a load like that
