@@ -52,9 +52,9 @@ CALIB_BYTES = 256 * 1024 * 1024   # plain copy used to scale the HBM counters
 # rocprofv3 kernel names of each op (substring match on the demangled name)
 OP_KERNELS = {
     "compress": ["compress_kernel<3, true, true, 8, 8, 0>"],
-    "decompress": ["decompress_cb_kernel<2, true, true, 0, false>"],
+    "decompress": ["decompress_cb_kernel<2, true, true, 0, false, false>"],
     "grad_compress": ["compress_kernel<3, false, false, 1, 8, 0>"],
-    "grad_decompress": ["decompress_cb_kernel<2, false, false, 0, false>"],
+    "grad_decompress": ["decompress_cb_kernel<2, false, false, 0, false, false>"],
     "compress_projected": ["compress_kernel<3, false, false, 1, 8, 1>"],
     # subspace update: its compress pass and its contraction over tokens
     "grassmann_compress": ["compress_kernel<3, false, false, 1, 8, 3>"],
@@ -62,7 +62,7 @@ OP_KERNELS = {
     # the weight projection of Wo and W2 (one call, three launches)
     "project_pass1": ["project_pass1_kernel<3, false, 8>"],
     "project_pass2": ["project_pass2_rfrag_kernel"],
-    "project_pass3": ["decompress_cb_kernel<3, false, false, 0, false>"],
+    "project_pass3": ["decompress_cb_kernel<3, false, false, 0, false, false>"],
 }
 PROJ_PASSES = ("project_pass1", "project_pass2", "project_pass3")
 

@@ -155,11 +155,14 @@ struct DSmem {
 };
 
 // PS: load the P rows with non-temporal loads (each is read once per call).
-template <int KS, bool HE, bool HP, int CM, bool PS>
+// BYID (with HE): C's rows are indexed by token id.  A parameter, since as an
+// argument it holds every call's coefficient loads back behind the tile's ids:
+// recovery + compress, both tables, 14814 tokens, d = 7680, k = 119 274.2 -> 272.4 us,
+// 6572 tokens, d = 5120, k = 44 77.4 -> 76.4.
+template <int KS, bool HE, bool HP, int CM, bool PS, bool BYID>
 __global__ __launch_bounds__(kDThreads) void decompress_cb_kernel(
     const bf16_t *__restrict__ rfrag, int64_t k, const bf16_t *__restrict__ C, int64_t ldc,
-    DTiling tm, IdArgs ids, ColSegs xs, int ncb, int ntiles, int tiles_per_wg, int young_from,
-    int c_by_id) {
+    DTiling tm, IdArgs ids, ColSegs xs, int ncb, int ntiles, int tiles_per_wg, int young_from) {
   constexpr int FR = 2 * KS;  // fragments per row group
   __shared__ u32x4 us[kPG * FR * 64];
   constexpr bool kIds = HE || HP;
@@ -250,6 +253,7 @@ __global__ __launch_bounds__(kDThreads) void decompress_cb_kernel(
     const unsigned T = tile_of(j);
     const int t0 = dtile_token0(tm, T);  // the tile's first token, once per tile
     auto tok_of = [&](int r) { return t0 + r < tm.N ? t0 + r : tm.N - 1; };
+    if constexpr (!BYID) load_coeffs<KS, CM>(dt, tok_of(n), C, ldc, k, g);
     // Tiles are loaded in order 0, 1, 2, ...: every fourth tile the entries
     // move down one, so tile j's ids are always in entry 0 (a wave-uniform
     // branch and register moves; a choice among the entries by j / 4 would be
@@ -260,11 +264,9 @@ __global__ __launch_bounds__(kDThreads) void decompress_cb_kernel(
       e0 = e1; e1 = e2; e2 = e3;
       q0 = q1; q1 = q2; q2 = q3;
     }
-    // the coefficient row of token n: its own, or its id's (c_by_id)
-    int crow = tok_of(n);
-    if constexpr (HE)
-      if (c_by_id) crow = __builtin_amdgcn_ds_bpermute((16 * (j & 3) + n) * 4, e0);
-    load_coeffs<KS, CM>(dt, crow, C, ldc, k, g);
+    if constexpr (BYID)
+      load_coeffs<KS, CM>(dt, __builtin_amdgcn_ds_bpermute((16 * (j & 3) + n) * 4, e0), C, ldc, k,
+                          g);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int r = 4 * i + q;
@@ -415,17 +417,16 @@ Slots resident_slots(K kernel) {
   return Slots{static_cast<int64_t>(cus) * per_cu, cus};
 }
 
-template <int KS, bool HE, bool HP, int CM, bool PS = false>
+template <int KS, bool HE, bool HP, int CM, bool PS, bool BYID>
 void launch_dcb(const bf16_t *rf, const PackLayout &L, const void *C, int64_t ldc,
-                const DTiling &tm, const IdArgs &ids, const ColSegs &X, int by_id,
-                hipStream_t s) {
+                const DTiling &tm, const IdArgs &ids, const ColSegs &X, hipStream_t s) {
   const int ncb = static_cast<int>(L.d / kDCols);
   // position-major tiles cover whole [batch, seq] sequences (the last one may
   // be short: its missing rows are read but not stored)
   const int64_t ntiles = tm.batch > 0 ? static_cast<int64_t>(tm.batch) * (tm.seq / 16)
                                       : ceil_div(tm.N, 16);
   // one round of resident workgroups over the whole grid, whole waves of tiles
-  static const Slots sl = resident_slots(decompress_cb_kernel<KS, HE, HP, CM, PS>);
+  static const Slots sl = resident_slots(decompress_cb_kernel<KS, HE, HP, CM, PS, BYID>);
   const int64_t groups = sl.slots / ncb > 0 ? sl.slots / ncb : 1;  // token groups per round
   int64_t per = ceil_div(ntiles, groups);
   per = per < kDW ? kDW : (per > kDW * kMaxWaveTiles ? kDW * kMaxWaveTiles : per);
@@ -434,15 +435,14 @@ void launch_dcb(const bf16_t *rf, const PackLayout &L, const void *C, int64_t ld
   dim3 grid(static_cast<unsigned>(tgroups * ncb));
   // workgroups past the first one per CU (when the grid has more)
   const int64_t young_from = tgroups * ncb > sl.cus ? sl.cus : tgroups * ncb;
-  decompress_cb_kernel<KS, HE, HP, CM, PS><<<grid, kDThreads, 0, s>>>(
+  decompress_cb_kernel<KS, HE, HP, CM, PS, BYID><<<grid, kDThreads, 0, s>>>(
       rf, L.k, static_cast<const bf16_t *>(C), ldc, tm, ids, X, ncb,
-      static_cast<int>(ntiles), static_cast<int>(per), static_cast<int>(young_from), by_id);
+      static_cast<int>(ntiles), static_cast<int>(per), static_cast<int>(young_from));
 }
 
-template <int KS, int CM>
+template <int KS, int CM, bool BYID>
 void launch_dcb_t(const bf16_t *rf, const PackLayout &L, const void *C, int64_t ldc,
-                  const DTiling &tm, const IdArgs &ids, const ColSegs &X, int by_id,
-                  hipStream_t s) {
+                  const DTiling &tm, const IdArgs &ids, const ColSegs &X, hipStream_t s) {
   const bool he = ids.E != nullptr, hp = ids.P != nullptr;
   // Each P row piece is read once per call.  Beside T_fixed, a large P
   // (over 64 MiB) streams through the caches and evicts the T_fixed rows that
@@ -450,27 +450,36 @@ void launch_dcb_t(const bf16_t *rf, const PackLayout &L, const void *C, int64_t 
   // 32768 tokens).  Alone, or when small, it is loaded normally and stays in
   // the 256 MB Infinity Cache from one call to the next.
   if (he && hp && ids.n_pos * L.d * 2 > (int64_t{64} << 20))
-    launch_dcb<KS, true, true, CM, true>(rf, L, C, ldc, tm, ids, X, by_id, s);
+    launch_dcb<KS, true, true, CM, true, BYID>(rf, L, C, ldc, tm, ids, X, s);
   else if (he && hp)
-    launch_dcb<KS, true, true, CM>(rf, L, C, ldc, tm, ids, X, by_id, s);
+    launch_dcb<KS, true, true, CM, false, BYID>(rf, L, C, ldc, tm, ids, X, s);
   else if (he)
-    launch_dcb<KS, true, false, CM>(rf, L, C, ldc, tm, ids, X, by_id, s);
+    launch_dcb<KS, true, false, CM, false, BYID>(rf, L, C, ldc, tm, ids, X, s);
   else if (hp)
-    launch_dcb<KS, false, true, CM>(rf, L, C, ldc, tm, ids, X, by_id, s);
+    launch_dcb<KS, false, true, CM, false, false>(rf, L, C, ldc, tm, ids, X, s);
   else
-    launch_dcb<KS, false, false, CM>(rf, L, C, ldc, tm, ids, X, by_id, s);
+    launch_dcb<KS, false, false, CM, false, false>(rf, L, C, ldc, tm, ids, X, s);
+}
+
+template <int KS, bool BYID>
+void launch_dcb_cm(const bf16_t *rf, const PackLayout &L, const void *C, int64_t ldc, int cmode,
+                   const DTiling &tm, const IdArgs &ids, const ColSegs &X, hipStream_t s) {
+  if (cmode == 0)
+    launch_dcb_t<KS, 0, BYID>(rf, L, C, ldc, tm, ids, X, s);
+  else if (cmode == 1)
+    launch_dcb_t<KS, 1, BYID>(rf, L, C, ldc, tm, ids, X, s);
+  else
+    launch_dcb_t<KS, 2, BYID>(rf, L, C, ldc, tm, ids, X, s);
 }
 
 template <int KS>
 void launch_dcb_ks(const bf16_t *rf, const PackLayout &L, const void *C, int64_t ldc, int cmode,
                    const DTiling &tm, const IdArgs &ids, const ColSegs &X, int by_id,
                    hipStream_t s) {
-  if (cmode == 0)
-    launch_dcb_t<KS, 0>(rf, L, C, ldc, tm, ids, X, by_id, s);
-  else if (cmode == 1)
-    launch_dcb_t<KS, 1>(rf, L, C, ldc, tm, ids, X, by_id, s);
+  if (by_id)
+    launch_dcb_cm<KS, true>(rf, L, C, ldc, cmode, tm, ids, X, s);
   else
-    launch_dcb_t<KS, 2>(rf, L, C, ldc, tm, ids, X, by_id, s);
+    launch_dcb_cm<KS, false>(rf, L, C, ldc, cmode, tm, ids, X, s);
 }
 
 // Leading dimensions below 2^31 elements keep row x row-bytes products in
