@@ -247,7 +247,9 @@ def sn_basis_pack(U: torch.Tensor, stream=None) -> Basis:
         raise SnError(2, f"invalid basis shape {d} x {k}")
     packed = torch.empty(nbytes, dtype=torch.uint8, device=U.device)
     _check(lib().sn_basis_pack(ptr, d, k, ldu, dt, packed.data_ptr(), nbytes, _stream(stream)))
-    return Basis(packed, d, k, dt)
+    basis = Basis.__new__(Basis)  # made to size: nothing to check
+    basis.packed, basis.d, basis.k, basis.dt = packed, d, k, dt
+    return basis
 
 
 def _tables(N, tok, E, pos, P, seq_len):

@@ -62,10 +62,8 @@ PackLayout pack_layout(int64_t d, int64_t k, int dt) {
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void pack_f32_kernel(const T *__restrict__ U, int64_t d,
-                                                       int64_t k, int64_t ldu,
-                                                       float *__restrict__ out) {
-  int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+__device__ __forceinline__ void pack_f32(int64_t idx, const T *__restrict__ U, int64_t d,
+                                         int64_t k, int64_t ldu, float *__restrict__ out) {
   if (idx >= d * k) return;
   int64_t r = idx / k, j = idx - r * k;
   out[idx] = to_f32(U[r * ldu + j]);
@@ -74,28 +72,28 @@ __global__ __launch_bounds__(256) void pack_f32_kernel(const T *__restrict__ U, 
 // The float32 fragment sections, one thread per 16-byte slot: kfrag32 slots
 // first, then rfrag32's.
 template <typename T>
-__global__ __launch_bounds__(256) void pack_frag32_kernel(const T *__restrict__ U, int64_t d,
-                                                          int64_t k, int64_t ldu, int kt,
-                                                          f32x4 *__restrict__ kfrag,
-                                                          f32x4 *__restrict__ rfrag) {
-  int64_t slot = (static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
+__device__ __forceinline__ void pack_frag32(int64_t slot, const T *__restrict__ U, int64_t d,
+                                            int64_t k, int64_t ldu, int kt,
+                                            f32x4 *__restrict__ kfrag,
+                                            f32x4 *__restrict__ rfrag) {
   const int64_t nk = (d + 31) / 32 * kt * 128, nr = (d + 15) / 16 * kt * 64;
   const bool second = slot >= nk;
   if (second) slot -= nk;
   if (second && slot >= nr) return;
   const int lane = static_cast<int>(slot & 63), g = lane >> 4, n = lane & 15;
   f32x4 v;
+  // 16-row blocks x column tiles: below 2^32, and a 32-bit division
+  const unsigned blk = static_cast<unsigned>(second ? slot >> 6 : slot >> 7);
+  const int64_t rb = blk / static_cast<unsigned>(kt), t = blk % static_cast<unsigned>(kt);
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     int64_t row, col;
     if (!second) {
-      const int64_t blk = slot >> 7;
-      row = 32 * (blk / kt) + 8 * g + 4 * ((slot >> 6) & 1) + e;
-      col = 16 * (blk % kt) + n;
+      row = 32 * rb + 8 * g + 4 * ((slot >> 6) & 1) + e;
+      col = 16 * t + n;
     } else {
-      const int64_t blk = slot >> 6;
-      row = 16 * (blk / kt) + 4 * (n & 3) + (n >> 2);
-      col = 16 * (blk % kt) + 4 * e + g;
+      row = 16 * rb + 4 * (n & 3) + (n >> 2);
+      col = 16 * t + 4 * e + g;
     }
     v[e] = row < d && col < k ? to_f32(U[row * ldu + col]) : 0.0f;
   }
@@ -103,10 +101,9 @@ __global__ __launch_bounds__(256) void pack_frag32_kernel(const T *__restrict__ 
 }
 
 // One thread per 8-element lane slot of a 1 KiB fragment block.
-__global__ __launch_bounds__(256) void pack_kfrag_kernel(const bf16_t *__restrict__ U, int64_t d,
-                                                         int64_t k, int64_t ldu, int kt,
-                                                         bf16_t *__restrict__ out) {
-  int64_t slot = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;  // (block, lane)
+__device__ __forceinline__ void pack_kfrag(int64_t slot, const bf16_t *__restrict__ U, int64_t d,
+                                           int64_t k, int64_t ldu, int kt,
+                                           bf16_t *__restrict__ out) {
   int64_t nblk = (d / 32) * kt;
   if (slot >= nblk * 64) return;
   int64_t blk = slot >> 6;
@@ -122,10 +119,9 @@ __global__ __launch_bounds__(256) void pack_kfrag_kernel(const bf16_t *__restric
   }
 }
 
-__global__ __launch_bounds__(256) void pack_rfrag_kernel(const bf16_t *__restrict__ U, int64_t d,
-                                                         int64_t k, int64_t ldu, int ks,
-                                                         bf16_t *__restrict__ out) {
-  int64_t slot = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+__device__ __forceinline__ void pack_rfrag(int64_t slot, const bf16_t *__restrict__ U, int64_t d,
+                                           int64_t k, int64_t ldu, int ks,
+                                           bf16_t *__restrict__ out) {
   int64_t nblk = (d / 32) * 2 * ks;
   if (slot >= nblk * 64) return;
   int64_t blk = slot >> 6;
@@ -143,15 +139,45 @@ __global__ __launch_bounds__(256) void pack_rfrag_kernel(const bf16_t *__restric
 }
 
 // [U | U] with zero columns up to 32 ks2, one thread per element.
-__global__ __launch_bounds__(256) void pack_uu_kernel(const bf16_t *__restrict__ U, int64_t d,
-                                                      int64_t k, int64_t ldu, int ks2,
-                                                      bf16_t *__restrict__ out) {
-  const int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+__device__ __forceinline__ void pack_uu(int64_t idx, const bf16_t *__restrict__ U, int64_t d,
+                                        int64_t k, int64_t ldu, int ks2,
+                                        bf16_t *__restrict__ out) {
   const int w = 32 * ks2;
   if (idx >= d * w) return;
   const int64_t r = idx / w;
   const int64_t j = idx - r * w;
   out[idx] = j < 2 * k ? U[r * ldu + (j < k ? j : j - k)] : bf16_t(0);
+}
+
+// Every section that is a copy of U, in one launch: each takes a range of the
+// workgroups.  With a launch per section the float32 operand sections made every
+// pack 3 to 5 us longer (back to back d = 256, k = 8, float32 10.9 -> 15.0 us; d = 4096,
+// k = 40, bf16 31.0 -> 34.0); in one launch 12.1 and 25.5, with the Gram matrix.
+struct PackSections {
+  float *f32;
+  f32x4 *kfrag32, *rfrag32;
+  bf16_t *kfrag, *rfrag, *uu;
+  int64_t end[5];  // workgroups up to and with f32, the float32 operands, kfrag, rfrag, uu
+};
+
+template <typename T>
+__global__ __launch_bounds__(256) void pack_kernel(const T *__restrict__ U, int64_t d, int64_t k,
+                                                   int64_t ldu, int kt, int ks, int ks2,
+                                                   PackSections p) {
+  const int64_t wg = static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x;
+  auto at = [&](int i) { return (wg - (i > 0 ? p.end[i - 1] : 0)) * 256 + threadIdx.x; };
+  if (wg < p.end[0])
+    pack_f32(at(0), U, d, k, ldu, p.f32);
+  else if (wg < p.end[1])
+    pack_frag32(at(1), U, d, k, ldu, kt, p.kfrag32, p.rfrag32);
+  else if constexpr (sizeof(T) == 2) {
+    if (wg < p.end[2])
+      pack_kfrag(at(2), U, d, k, ldu, kt, p.kfrag);
+    else if (wg < p.end[3])
+      pack_rfrag(at(3), U, d, k, ldu, ks, p.rfrag);
+    else if (wg < p.end[4])
+      pack_uu(at(4), U, d, k, ldu, ks2, p.uu);
+  }
 }
 
 // U^T U - I from the float32 section (exact copies of the stored U), as a
@@ -187,43 +213,33 @@ __global__ __launch_bounds__(kGramThreads) void pack_gram_kernel(const float *__
 hipError_t launch_pack(const PackLayout &L, const void *U, int64_t ldu, void *packed,
                        hipStream_t s) {
   char *base = static_cast<char *>(packed);
-  int64_t n = L.d * L.k;
-  dim3 grid(static_cast<unsigned>(ceil_div(n, 256)));
-  if (L.dt == 0)
-    pack_f32_kernel<float><<<grid, 256, 0, s>>>(static_cast<const float *>(U), L.d, L.k, ldu,
-                                                reinterpret_cast<float *>(base + L.off_f32));
-  else
-    pack_f32_kernel<bf16_t><<<grid, 256, 0, s>>>(static_cast<const bf16_t *>(U), L.d, L.k, ldu,
-                                                 reinterpret_cast<float *>(base + L.off_f32));
-  {
-    const int64_t slots = ceil_div(L.d, 32) * L.kt * 128 + ceil_div(L.d, 16) * L.kt * 64;
-    // 8 threads per row and column tile: more than one grid dimension's 2^32 above
-    // 2^29 rows
-    const int64_t blocks = ceil_div(slots, 256);
-    const dim3 gf(static_cast<unsigned>(grid_x(blocks)), grid_more(blocks));
-    f32x4 *kf = reinterpret_cast<f32x4 *>(base + L.off_kfrag32);
-    f32x4 *rf = reinterpret_cast<f32x4 *>(base + L.off_rfrag32);
-    if (L.dt == 0)
-      pack_frag32_kernel<float><<<gf, 256, 0, s>>>(static_cast<const float *>(U), L.d, L.k, ldu,
-                                                   L.kt, kf, rf);
-    else
-      pack_frag32_kernel<bf16_t><<<gf, 256, 0, s>>>(static_cast<const bf16_t *>(U), L.d, L.k, ldu,
-                                                    L.kt, kf, rf);
-  }
+  PackSections p{};
+  p.f32 = reinterpret_cast<float *>(base + L.off_f32);
+  p.kfrag32 = reinterpret_cast<f32x4 *>(base + L.off_kfrag32);
+  p.rfrag32 = reinterpret_cast<f32x4 *>(base + L.off_rfrag32);
+  // threads of each section: an element, or a 16-byte slot
+  int64_t n[5] = {L.d * L.k, ceil_div(L.d, 32) * L.kt * 128 + ceil_div(L.d, 16) * L.kt * 64, 0, 0,
+                  0};
   if (L.mfma) {
-    const bf16_t *Ub = static_cast<const bf16_t *>(U);
-    int64_t slots = (L.d / 32) * L.kt * 64;
-    pack_kfrag_kernel<<<dim3(static_cast<unsigned>(ceil_div(slots, 256))), 256, 0, s>>>(
-        Ub, L.d, L.k, ldu, L.kt, reinterpret_cast<bf16_t *>(base + L.off_kfrag));
-    slots = (L.d / 32) * 2 * L.ks * 64;
-    pack_rfrag_kernel<<<dim3(static_cast<unsigned>(ceil_div(slots, 256))), 256, 0, s>>>(
-        Ub, L.d, L.k, ldu, L.ks, reinterpret_cast<bf16_t *>(base + L.off_rfrag));
+    p.kfrag = reinterpret_cast<bf16_t *>(base + L.off_kfrag);
+    p.rfrag = reinterpret_cast<bf16_t *>(base + L.off_rfrag);
+    n[2] = (L.d / 32) * L.kt * 64;
+    n[3] = (L.d / 32) * 2 * L.ks * 64;
     if (L.ks2 > 0) {
-      const int64_t nu = L.d * 32 * L.ks2;
-      pack_uu_kernel<<<dim3(static_cast<unsigned>(ceil_div(nu, 256))), 256, 0, s>>>(
-          Ub, L.d, L.k, ldu, L.ks2, reinterpret_cast<bf16_t *>(base + L.off_uu));
+      p.uu = reinterpret_cast<bf16_t *>(base + L.off_uu);
+      n[4] = L.d * 32 * L.ks2;
     }
   }
+  int64_t wgs = 0;
+  for (int i = 0; i < 5; ++i) p.end[i] = wgs += ceil_div(n[i], 256);
+  // (8 threads per row and column tile alone outgrow a grid dimension above 2^29 rows)
+  const dim3 grid(static_cast<unsigned>(grid_x(wgs)), grid_more(wgs));
+  if (L.dt == 0)
+    pack_kernel<float><<<grid, 256, 0, s>>>(static_cast<const float *>(U), L.d, L.k, ldu, L.kt,
+                                            L.ks, L.ks2, p);
+  else
+    pack_kernel<bf16_t><<<grid, 256, 0, s>>>(static_cast<const bf16_t *>(U), L.d, L.k, ldu, L.kt,
+                                             L.ks, L.ks2, p);
   const int64_t kp = 16 * L.kt;
   pack_gram_kernel<<<dim3(static_cast<unsigned>(kp)), kGramThreads, 0, s>>>(
       reinterpret_cast<const float *>(base + L.off_f32), L.d, L.k, kp,
