@@ -719,11 +719,56 @@ __global__ __launch_bounds__(256) void decompress_f64_kernel(
   }
 }
 
+// Few values: a thread per value, the same sum in float64.  Such a launch is a chain
+// of latencies, shorter without the fragments' way through LDS, the MFMAs and the
+// edges of the tiles; with more values or columns of U the products decide.  In a
+// graph, matrix cores / a thread per value (a thread per value in compensated float32
+// sums, which every launch once took, first):
+//   bf16, both tables   d = 131, k = 3, 160 tokens   2.74   4.32 / 2.86 us
+//                       d = 384, k = 6, 512 tokens   3.57   4.48 / 3.52
+//                       d = 384, k = 4, 1300 tokens         4.43 / 4.82
+//   float32, no tables  d = 384, k = 6, 512 tokens   2.81   2.99 / 2.92
+//                       d = 600, k = 12, 290 tokens         3.08 / 3.19
+//                       d = 384, k = 6, 2048 tokens  5.20   3.56 / 5.43
+inline bool few_values(int64_t values, int64_t k) {
+  return values <= (int64_t{1} << 19) && values * k <= (int64_t{5} << 18);
+}
+
+template <typename T, bool TAB>
+__global__ __launch_bounds__(256) void decompress_few_kernel(
+    const float *__restrict__ U, unsigned d, int k, const T *__restrict__ C, unsigned total,
+    int64_t ldc, IdArgs ids, T *__restrict__ X, int64_t ldx) {
+  const unsigned idx = blockIdx.x * 256 + threadIdx.x;
+  if (idx >= total) return;
+  const unsigned i = idx / d, c = idx - i * d;
+  const T *cr = C + i * ldc;
+  const float *ur = U + static_cast<int64_t>(c) * k;
+  double v = 0.0;
+  if constexpr (TAB) {
+    const Rows<T> rw = resolve_rows<T>(i, ids, static_cast<const T *>(nullptr));
+    if (ids.P) v += static_cast<double>(to_f32(rw.p[c]));
+    if (ids.E) v += static_cast<double>(to_f32(rw.e[c]));
+  }
+#pragma unroll 8
+  for (int j = 0; j < k; ++j)
+    v = fma(static_cast<double>(ur[j]), static_cast<double>(to_f32(cr[j])), v);
+  X[i * ldx + c] = from_f64<T>(v);
+}
+
 template <typename T, bool TAB>
 hipError_t decompress_f64(const PackLayout &L, const void *packed, const void *C, int64_t N,
                           int64_t ldc, const IdArgs &ids, void *X, int64_t ldx, hipStream_t s) {
   const f32x4 *rf =
       reinterpret_cast<const f32x4 *>(static_cast<const char *>(packed) + L.off_rfrag32);
+  const int64_t total = N * L.d;
+  if (few_values(total, L.k)) {
+    const float *u32 =
+        reinterpret_cast<const float *>(static_cast<const char *>(packed) + L.off_f32);
+    decompress_few_kernel<T, TAB><<<dim3(static_cast<unsigned>(ceil_div(total, 256))), 256, 0, s>>>(
+        u32, static_cast<unsigned>(L.d), static_cast<int>(L.k), static_cast<const T *>(C),
+        static_cast<unsigned>(total), ldc, ids, static_cast<T *>(X), ldx);
+    return hipGetLastError();
+  }
   // column ranges: about 4 workgroups (16 waves) a CU, and as many pairs as
   // the LDS allotment holds
   const int64_t tgroups = ceil_div(N, 64), pairs = ceil_div(L.d, 32);

@@ -395,6 +395,34 @@ def test_generic_kernel_edges(dtype, d, k, n, pad, tables):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d,k,n,pad", [(1, 1, 1, 0), (131, 10, 1000, 1), (131, 10, 1001, 1),  # 5 2^18 products
+                                       (8, 2, 65536, 0), (8, 2, 65537, 0), (7, 3, 75001, 2),  # 2^19 values
+                                       (33, 15, 2701, 3), (49, 17, 1601, 0), (95, 49, 290, 5),
+                                       (31, 20, 2129, 1)])
+def test_generic_recovery_of_few_and_many_values(dtype, d, k, n, pad):
+    """The generic recovery on both sides of the rule that gives each value a
+    thread of its own, and past it partial column tiles, ranks and token groups of
+    the matrix-core form; rows wider than d stay as they were past it."""
+    log(f"[generic recovery] {dtype} d={d} k={k} n={n} pad={pad}")
+    st, o, tok, pos = _small(d, k, n, dtype=dtype, seed=d + k + n)
+    basis = sn.sn_basis_pack(dev(st["U"], dtype))
+    E, P, C = (dev(st[x], dtype) for x in "EPC")
+    for t in ("EP", "E", "P", ""):
+        out = torch.full((n, d + pad), 7.0, device="cuda", dtype=C.dtype)
+        sn.sn_decompress(basis, C, tok=ids(tok), E=E if "E" in t else None,
+                         P=P if "P" in t else None, pos=ids(pos), out=out[:, :d])
+        assert bool((out[:, d:] == 7.0).all())
+        ref = oracle.decompress(o["C"], o["U"], tok, o["E"] if "E" in t else None,
+                                o["P"] if "P" in t else None, pos=pos)
+        if dtype == "bf16":
+            assert_parity(host(out[:, :d]), oracle.round_to(ref, dtype), dtype, f"recovery {t!r}")
+        else:  # one rounding of a float64 sum of k + 2 terms
+            terms = np.abs(o["C"]) @ np.abs(o["U"]).T + np.abs(ref)
+            err = np.abs(host(out[:, :d]) - ref)
+            assert np.all(err <= 2.0 ** -24 * np.abs(ref) + 1e-14 * terms + 1e-45), t
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("d,k,m,pad", [(7, 3, 5, 0), (31, 4, 64, 1), (33, 17, 65, 3), (161, 33, 1, 0),
                                        (600, 70, 130, 1), (1000, 129, 67, 5), (300, 256, 40, 0)])
 def test_generic_weights_edges(dtype, d, k, m, pad):
